@@ -958,23 +958,25 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
             (rc = check_device_ptr(g.vis, "vis", i)))
             return rc;
     }
-    int64_t items = 0;
+    // the limit of one call: 2^31 blocks of 64 points x 16 columns
+    int64_t blocks = 0;
     for (const rt::VisImage& m : tab)
-        items += static_cast<int64_t>((m.K + 63) / 64) * ((m.nx + rt::kVisCols - 1) / rt::kVisCols);
-    if (items >= (int64_t(1) << 31)) return fail(RT_ERR_ARG, "too much visibility work for one call");
-    int32_t n_items = 0;
-    int64_t n_part = 0;
-    rt::vis_layout(tab.data(), n, &n_items, &n_part);
+        blocks += static_cast<int64_t>((m.K + 63) / 64) * ((m.nx + 15) / 16);
+    int64_t n_items = 0, n_part = 0, n_fold = 0;
+    rt::vis_layout(tab.data(), n, &n_items, &n_part, &n_fold);
+    if (blocks >= (int64_t(1) << 31) || n_items >= (int64_t(1) << 31))
+        return fail(RT_ERR_ARG, "too much visibility work for one call");
     auto up256 = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t tab_bytes = up256(sizeof(rt::VisImage) * n);
     const size_t flux_bytes = up256(sizeof(double) * rt::kVisFluxBlocks * n);
     const size_t part_bytes = up256(sizeof(double2) * static_cast<size_t>(n_part));
+    const size_t fold_bytes = up256(sizeof(double) * static_cast<size_t>(n_fold));
+    const size_t bytes = tab_bytes + flux_bytes + part_bytes + fold_bytes;
     void* mem = nullptr;
-    hipError_t e = hipMallocAsync(&mem, tab_bytes + flux_bytes + part_bytes, stream);
+    hipError_t e = hipMallocAsync(&mem, bytes, stream);
     if (e != hipSuccess || !mem) {
         (void)hipGetLastError();
-        return fail(RT_ERR_ALLOC, "stream-ordered allocation of %zu visibility bytes failed",
-                    tab_bytes + flux_bytes + part_bytes);
+        return fail(RT_ERR_ALLOC, "stream-ordered allocation of %zu visibility bytes failed", bytes);
     }
     char* base = static_cast<char*>(mem);
     auto bail = [&](int code) {
@@ -989,8 +991,10 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
                             stream)) != hipSuccess ||
         (e = hipEventRecord(g_staging.ready, stream)) != hipSuccess)
         return bail(hip_fail(e, "visibility table upload"));
-    e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), n, n_items, max_k,
+    e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), n,
+                              static_cast<int32_t>(n_items), max_k,
                               reinterpret_cast<double2*>(base + tab_bytes + flux_bytes),
+                              reinterpret_cast<double*>(base + tab_bytes + flux_bytes + part_bytes),
                               reinterpret_cast<double*>(base + tab_bytes), stream);
     if (e != hipSuccess) return bail(hip_fail(e, "visibility kernel launch"));
     if ((e = hipFreeAsync(mem, stream)) != hipSuccess) return hip_fail(e, "hipFreeAsync");
@@ -1277,7 +1281,10 @@ int rt_visibility_rings(const double* intensity, const rt_image_params* params, 
         (rc = check_device_ptr(cut, "cut", 0)))
         return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int64_t n = static_cast<int64_t>(n_q) * n_angles;
+    // The image is real, so V(-u, -v) is V(u, v)'s conjugate: with an even number
+    // of angles the second half circle repeats the first one's amplitudes.
+    const int32_t n_dirs = n_angles % 2 == 0 ? n_angles / 2 : n_angles;
+    const int64_t n = static_cast<int64_t>(n_q) * n_dirs;
     void* mem = nullptr;
     hipError_t e = hipMallocAsync(&mem, sizeof(double) * 3 * n, stream);
     if (e != hipSuccess || !mem) {
@@ -1290,13 +1297,13 @@ int rt_visibility_rings(const double* intensity, const rt_image_params* params, 
         (void)hipFreeAsync(mem, stream);
         return code;
     };
-    if ((e = rt::launch_ring_points(q, n_q, n_angles, uv, stream)) != hipSuccess)
+    if ((e = rt::launch_ring_points(q, n_q, n_angles, n_dirs, uv, stream)) != hipSuccess)
         return bail(hip_fail(e, "ring point kernel launch"));
     const rt_vis_image img{intensity, uv, amp, nullptr, params->nx, params->ny,
                            static_cast<int32_t>(n), 0, params->x_min, params->x_max,
                            params->y_min, params->y_max};
     if ((rc = visibility_images(&img, 1, stream)) != RT_OK) return bail(rc);
-    if ((e = rt::launch_ring_average(amp, n_q, n_angles, avg, cut, stream)) != hipSuccess)
+    if ((e = rt::launch_ring_average(amp, n_q, n_dirs, avg, cut, stream)) != hipSuccess)
         return bail(hip_fail(e, "ring average kernel launch"));
     if ((e = hipFreeAsync(mem, stream)) != hipSuccess) return hip_fail(e, "hipFreeAsync");
     return RT_OK;

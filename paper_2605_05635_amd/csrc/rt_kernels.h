@@ -117,33 +117,35 @@ hipError_t launch_reduce(const ImageConst& c, const double* intensity, double* p
 // Normalised visibility amplitudes (Sec. 6.4) of n_img images in one launch
 // sequence.  VisImage holds one image (device pointers I [ny][nx], uv [K][2],
 // amp [K] or null, vis [K][2] or null; the screen of its pixel centres);
-// vis_layout fills the work-item and partial-sum offsets of a host table and
-// returns the totals.  launch_visibility runs the flux partials (fpart:
-// kVisFluxBlocks doubles per image), the partial sums (part: n_part double2)
-// and the finish on the device copy d_tab of that table; max_k is the
-// largest K.  Deterministic.
-constexpr int kVisCols = 16;          // image columns per work item
-constexpr int kVisFluxBlocks = 64;    // flux partials per image
+// vis_layout fills the work split of a host table and its offsets and returns
+// the totals.  launch_visibility runs the row fold with the flux partials
+// (fold: n_fold doubles; fpart: kVisFluxBlocks doubles per image), the partial
+// sums (part: n_part double2) and the finish on the device copy d_tab of that
+// table; max_k is the largest K.  Deterministic.
+constexpr int kVisFluxBlocks = 256;   // flux partials per image
 struct VisImage {
     const double* I;
     const double* uv;
     double* amp;
     double* vis;
     int32_t nx, ny, K;
-    int32_t nkg, ncb;                 // point groups of 64, column blocks of kVisCols
+    int32_t nct, nq;                  // 16-column tiles, quads of folded rows
+    int32_t nkg, ncb, nseg;           // point groups, column blocks, row segments
     int32_t item0;                    // first work item (wavefront) of the image
-    int64_t part0;                    // first partial sum: [ncb][K]
+    int64_t part0;                    // first partial sum: [ncb nseg][K]
+    int64_t fold0;                    // first folded value: [nct][nq][2][64]
     double x0, dx, y0, dy;
 };
-void vis_layout(VisImage* tab, int32_t n_img, int32_t* n_items, int64_t* n_part);
+void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold);
 hipError_t launch_visibility(const VisImage* d_tab, int32_t n_img, int32_t n_items, int32_t max_k,
-                             double2* part, double* fpart, hipStream_t stream);
-// Points on n_q rings (radius q[j], device) at n_angles angles 2 pi a / n_angles:
-// uv [n_q n_angles][2]; and the average of amp over each ring's angles (avg)
-// with its amplitude at angle 0 (cut), either output optional.
-hipError_t launch_ring_points(const double* q, int32_t n_q, int32_t n_angles, double* uv,
-                              hipStream_t stream);
-hipError_t launch_ring_average(const double* amp, int32_t n_q, int32_t n_angles, double* avg,
+                             double2* part, double* fold, double* fpart, hipStream_t stream);
+// Points on n_q rings (radius q[j], device), the first n_dirs of the angles
+// 2 pi a / n_angles: uv [n_q n_dirs][2]; and the average of amp over each
+// ring's n_dirs points (avg) with its amplitude at angle 0 (cut), either
+// output optional.
+hipError_t launch_ring_points(const double* q, int32_t n_q, int32_t n_angles, int32_t n_dirs,
+                              double* uv, hipStream_t stream);
+hipError_t launch_ring_average(const double* amp, int32_t n_q, int32_t n_dirs, double* avg,
                                double* cut, hipStream_t stream);
 
 // Mixed precision.  trace32: the binary32 pass over the screen (order of

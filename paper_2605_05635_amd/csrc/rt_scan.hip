@@ -17,7 +17,7 @@ using scan::delta;
 // Grid intervals k = 1..n of the two serial searches, by their own loop
 // conditions, counted at compile time.  (Counted on the device, by every
 // wavefront and for both roots, the 59,986 dependent add-and-compare steps
-// took two thirds of the kernel: 3.58 ms for 4096 points, 1.19 ms without.)
+// took three quarters of the kernel: 3.44 ms for 4096 points, 0.80 ms without.)
 constexpr int root_intervals() {
     int n = 0;
     while (50.0 - (n + 1) * 1e-2 >= 0.05 - 1e-12) ++n;

@@ -3,24 +3,33 @@
 // + v Y)) dX dY and amp(u,v) = |V(u,v)| / |V(0,0)|, the midpoint rule, at K
 // arbitrary (u, v) points per image; many images in one launch.
 //
-// The phase factorises over the screen axes: with D_k(x) = sum_y I[y][x]
-// exp(-2 pi i v_k Y_y), V_k = dX dY sum_x exp(-2 pi i u_k X_x) D_k(x).  The
-// contraction over y (2 K nx ny multiply-adds) is the work; it is done on the
-// binary64 vector ALU with the phases generated in registers, never stored:
-//   * one wavefront per work item = (image, 64 consecutive points, a block of
-//     kVisCols = 16 consecutive columns); lane j owns point k = 64 g + j;
-//   * the 16 pixels of a row in the block are the same for every lane: they
-//     are read with two 64-byte scalar loads (wave-uniform address, the
-//     scalar cache) and enter the multiply-adds as scalar operands;
-//   * each lane advances its row phase exp(-2 pi i v Y) from one row to the
-//     next by one complex multiplication with exp(-2 pi i v dY) (four
-//     operations shared by the 16 columns), re-seeded from an exact sine and
-//     cosine every kReseed rows, so the recurrence error stays ~1e-14;
-//   * the column phases exp(-2 pi i u X) of the block's columns likewise.
-// Each work item writes one partial sum per point; a second kernel adds a
-// point's partials over the column blocks in index order, scales by dX dY and
-// divides by the flux |V(0,0)| from a fixed-order reduction of the image.
-// Deterministic run to run; no matrix cores (VALU only).
+// The phase factorises over the screen axes, and the pixel rows lie in pairs
+// Y_c -+ a about the screen's centre row Y_c.  With S = I(Y_c - a) + I(Y_c + a)
+// and D = I(Y_c - a) - I(Y_c + a) of each pair,
+//   sum_y exp(-2 pi i v Y) I = exp(-2 pi i v Y_c) sum_a [cos(2 pi v a) S + i sin(2 pi v a) D],
+// two real products per pixel pair where the plain sum takes four, so the work
+// is two real matrix products per image (K points x folded rows x columns),
+//   R_k(x) = sum_a cos(2 pi v_k a) S(a, x),   J_k(x) = sum_a sin(2 pi v_k a) D(a, x),
+// done on the matrix cores in binary64 (v_mfma_f64_16x16x4, which accumulates
+// with fused multiply-adds like the vector unit):
+//   * a first pass writes S and D in the order the matrix instructions read
+//     them (16 columns x 4 rows = one 512-byte load of a wavefront) and sums
+//     the flux |V(0,0)| on the way;
+//   * one wavefront per work item = (image, 32 points, 64 columns, a segment
+//     of the folded rows), 16 accumulator tiles; a lane generates its own
+//     elements of the left operand, cos and sin of its point's phase at its
+//     row, stepped four rows by one complex multiplication and re-seeded from
+//     an exact sine and cosine every kReseed rows (recurrence error ~1e-14),
+//     in the shadow of the matrix instructions;
+//   * the item's 64 columns are then summed with exp(-2 pi i (u X + v Y_c)).
+// Each work item writes one partial sum per point; a last kernel adds a
+// point's partials in index order, scales by dX dY and divides by the flux.
+// Deterministic run to run, and the split of an image depends on it alone.
+//
+// Bound by the binary64 matrix rate: a probe of independent
+// v_mfma_f64_16x16x4 reaches 77 TFLOP/s on this card (71 with one wavefront
+// per SIMD, so two waves suffice), where dependent-free vector FMAs hold 52
+// under the same power limit.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -33,110 +42,61 @@ namespace {
 
 constexpr double kTwoPi = 6.283185307179586;
 constexpr int kVisThreads = 256;            // four work items (wavefronts) per block
-constexpr int kReseed = 64;                 // columns between exact column phases
+constexpr int kReseed = 16;                 // row quads between exact phases
+constexpr int kPT = 2, kCT = 4;             // 16-point and 16-column tiles of a work item
 
-// Image values are read through the constant address space: wave-uniform
-// loads from it are scalar loads (the image is not written while the kernel
-// runs).  A work item's kVisCols consecutive pixels of a row are 16 doubles
-// = two 64-byte scalar loads.
-typedef const __attribute__((address_space(4))) double* ConstPix;
-static_assert(kVisCols == 16, "the row loads below move 16 doubles");
+typedef double Acc __attribute__((ext_vector_type(4)));
 
-struct Row16 {
-    double v[16];
-};
-
-// Waits for every scalar load in flight (s_waitcnt lgkmcnt(0), the other
-// counters left alone).
-__device__ __forceinline__ void wait_scalar_loads() { __builtin_amdgcn_s_waitcnt(0xc07f); }
-
-// One row's contribution: D(c) += (c_ + i s_) a[c].
-__device__ __forceinline__ void add_row(const Row16& a, double c_, double s_,
-                                        double* __restrict__ are, double* __restrict__ aim) {
-#pragma unroll
-    for (int j = 0; j < kVisCols; ++j) {
-        are[j] = fma(c_, a.v[j], are[j]);
-        aim[j] = fma(s_, a.v[j], aim[j]);
-    }
-}
-
-// D(c) += exp(i t Y_y) I[y][c] over all rows y for the 16 full columns at p
-// (row stride nx): each row's 16 pixels are two 64-byte scalar loads, issued
-// one row ahead of their use (rows taken in pairs, so that the wait before a
-// row's multiply-adds covers only loads issued a row earlier; the loads ahead
-// are clamped to the last row).
-__device__ __forceinline__ void accumulate_rows_full(ConstPix p, int32_t nx, int32_t ny, double y0,
-                                                     double dy, double t, double* __restrict__ are,
-                                                     double* __restrict__ aim) {
-    double ws, wc;
-    dm::sincos(t * dy, &ws, &wc);
-    auto row = [&](int32_t y) {
-        const int32_t yy = y < ny ? y : ny - 1;
-        const ConstPix q = p + static_cast<int64_t>(yy) * nx;
-        Row16 a;
-#pragma unroll
-        for (int j = 0; j < kVisCols; ++j) a.v[j] = q[j];
-        return a;
-    };
-    double s = 0.0, c = 1.0;
-    Row16 A = row(0), B;
-    for (int32_t y = 0; y < ny; y += 2) {
-        if ((y & (kReseed - 1)) == 0)   // exact phase every kReseed rows
-            dm::sincos(t * (y0 + (static_cast<double>(y) + 0.5) * dy), &s, &c);
-        wait_scalar_loads();
-        B = row(y + 1);
-        __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the multiply-adds
-        add_row(A, c, s, are, aim);
-        double cn = c * wc - s * ws;
-        s = s * wc + c * ws;
-        c = cn;
-        // the odd row past the end of an odd-height screen enters with weight 0
-        const double wB = y + 1 < ny ? 1.0 : 0.0;
-        wait_scalar_loads();
-        A = row(y + 2);
-        __builtin_amdgcn_sched_barrier(0);
-        add_row(B, c * wB, s * wB, are, aim);
-        cn = c * wc - s * ws;
-        s = s * wc + c * ws;
-        c = cn;
-    }
-}
-
-// As accumulate_rows_full for the screen's last column block, narrower than
-// 16 columns: only its first ncols pixels of a row are read.
-__device__ __forceinline__ void accumulate_rows_tail(ConstPix p, int32_t nx, int32_t ny,
-                                                     int32_t ncols, double y0, double dy, double t,
-                                                     double* __restrict__ are,
-                                                     double* __restrict__ aim) {
-    double ws, wc;
-    dm::sincos(t * dy, &ws, &wc);
-    for (int32_t yb = 0; yb < ny; yb += kReseed) {
-        const double Y = y0 + (static_cast<double>(yb) + 0.5) * dy;
-        double s, c;
-        dm::sincos(t * Y, &s, &c);
-        const int32_t ye = yb + kReseed < ny ? yb + kReseed : ny;
-        for (int32_t y = yb; y < ye; ++y) {
-            Row16 a;
-#pragma unroll
-            for (int j = 0; j < kVisCols; ++j) a.v[j] = j < ncols ? p[j] : 0.0;
-            add_row(a, c, s, are, aim);
-            const double cn = c * wc - s * ws;
-            s = s * wc + c * ws;
-            c = cn;
-            p += nx;
+// Folded rows of an image in matrix-operand order: column tile t and row quad
+// q hold 64 values of S then 64 of D, value 16 r + c for row 4 q + r and column
+// 16 t + c (zero beyond the screen), which is the lane order of the right
+// operand.  Block b of image i takes every kVisFluxBlocks-th group of four
+// (tile, quad) cells and leaves the sum of its S values, a partial of the
+// flux, in fpart[i kVisFluxBlocks + b] (fixed order).
+__global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* __restrict__ tab,
+                                                               double* __restrict__ fold,
+                                                               double* __restrict__ fpart) {
+    __shared__ double sh[kVisThreads];
+    const VisImage& m = tab[blockIdx.y];
+    const int32_t nx = m.nx, ny = m.ny, nq = m.nq;
+    const int32_t h = (ny + 1) / 2;
+    const int64_t cells = static_cast<int64_t>(m.nct) * nq;
+    const int lane = static_cast<int>(threadIdx.x & 63), r = lane >> 4, col = lane & 15;
+    double sum = 0.0;
+    for (int64_t cell = 4 * static_cast<int64_t>(blockIdx.x) + (threadIdx.x >> 6); cell < cells;
+         cell += 4 * kVisFluxBlocks) {
+        const int32_t t = static_cast<int32_t>(cell / nq), q = static_cast<int32_t>(cell - static_cast<int64_t>(t) * nq);
+        const int32_t x = 16 * t + col, y = 4 * q + r;
+        double S = 0.0, D = 0.0;
+        if (x < nx && y < h) {
+            const int32_t z = ny - 1 - y;
+            const double a = m.I[static_cast<int64_t>(y) * nx + x];
+            if (z > y) {
+                const double b = m.I[static_cast<int64_t>(z) * nx + x];
+                S = a + b;
+                D = a - b;
+            } else {
+                S = a;   // the centre row of an odd screen
+            }
         }
+        double* out = fold + m.fold0 + cell * 128 + lane;
+        out[0] = S;
+        out[64] = D;
+        sum += S;
     }
+    sh[threadIdx.x] = sum;
+    __syncthreads();
+    for (int w = kVisThreads / 2; w > 0; w >>= 1) {
+        if (static_cast<int>(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) fpart[blockIdx.y * kVisFluxBlocks + blockIdx.x] = sh[0];
 }
 
-// Partial sums of V over one work item: the kVisCols columns [c0, c0 + 16)
-// of the image, all rows, for the 64 points of the item's group (one per
-// lane).  With D_k(c) = sum_y exp(-2 pi i v_k Y_y) I[y][c], each lane forms
-// D_k over the rows (two multiply-adds per pixel with the row's phase), then
-// the partial V_k = sum_c exp(-2 pi i u_k X_c) D_k(c).
-__global__ __launch_bounds__(kVisThreads) void vis_partial_kernel(
+// Partial sums of V over one work item.
+__global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void vis_partial_kernel(
     const VisImage* __restrict__ tab, int32_t n_img, int32_t n_items,
-    double2* __restrict__ part) {
-    // work item = wavefront; made explicitly wave-uniform for the scalar path
+    const double* __restrict__ fold, double2* __restrict__ part) {
     const int32_t w = __builtin_amdgcn_readfirstlane(
         static_cast<int32_t>(blockIdx.x) * (kVisThreads / 64) + static_cast<int32_t>(threadIdx.x >> 6));
     if (w >= n_items) return;
@@ -146,78 +106,134 @@ __global__ __launch_bounds__(kVisThreads) void vis_partial_kernel(
         if (tab[mid].item0 <= w) lo = mid; else hi = mid - 1;
     }
     const VisImage& m = tab[lo];
+    // items: point groups fastest, so a block's wavefronts read the same rows
     const int32_t local = w - m.item0;
-    const int32_t cb = local / m.nkg, kg = local - cb * m.nkg;
-    const int32_t k = kg * 64 + static_cast<int32_t>(__lane_id());
-    const bool valid = k < m.K;
-    const double u = valid ? m.uv[2 * k] : 0.0;
-    const double v = valid ? m.uv[2 * k + 1] : 0.0;
-    const int32_t nx = m.nx;
-    const int32_t c0 = cb * kVisCols;
-    const int32_t ncols = nx - c0 < kVisCols ? nx - c0 : kVisCols;
-    double are[kVisCols], aim[kVisCols];
+    const int32_t cell = local / m.nkg, kg = local - cell * m.nkg;
+    const int32_t cb = cell / m.nseg, seg = cell - cb * m.nseg;
+    const int32_t K = m.K, nq = m.nq;
+    const int lane = __lane_id(), r = lane >> 4, i16 = lane & 15;
+    const int32_t q0 = static_cast<int32_t>(static_cast<int64_t>(nq) * seg / m.nseg);
+    const int32_t q1 = static_cast<int32_t>(static_cast<int64_t>(nq) * (seg + 1) / m.nseg);
+    const int32_t ct = m.nct - cb * kCT < kCT ? m.nct - cb * kCT : kCT;   // column tiles of this item
+    const int32_t k0 = kg * 16 * kPT;
+
+    // left operand: lane (r, i16) holds point k0 + 16 p + i16 at row 4 q + r
+    double tv[kPT], c[kPT], s[kPT], wc[kPT], ws[kPT];
 #pragma unroll
-    for (int c = 0; c < kVisCols; ++c) are[c] = aim[c] = 0.0;
-    // rows: exp(i t Y) with t = -2 pi v
-    const ConstPix p = (ConstPix)(m.I + c0);
-    if (ncols == kVisCols)
-        accumulate_rows_full(p, nx, m.ny, m.y0, m.dy, -kTwoPi * v, are, aim);
-    else
-        accumulate_rows_tail(p, nx, m.ny, ncols, m.y0, m.dy, -kTwoPi * v, are, aim);
-    // columns: exp(i t' X) with t' = -2 pi u, stepped by exp(i t' dX)
-    const double tx = -kTwoPi * u;
-    double vs, vc, xs, xc;
-    dm::sincos(tx * m.dx, &vs, &vc);
-    dm::sincos(tx * (m.x0 + (static_cast<double>(c0) + 0.5) * m.dx), &xs, &xc);
-    double re = 0.0, im = 0.0;
-#pragma unroll
-    for (int j = 0; j < kVisCols; ++j) {
-        if (j < ncols) {
-            re += xc * are[j] - xs * aim[j];
-            im += xc * aim[j] + xs * are[j];
-        }
-        const double cn = xc * vc - xs * vs;
-        xs = xs * vc + xc * vs;
-        xc = cn;
+    for (int p = 0; p < kPT; ++p) {
+        const int32_t k = k0 + 16 * p + i16;
+        tv[p] = k < K ? kTwoPi * m.uv[2 * k + 1] : 0.0;
+        dm::sincos(tv[p] * (4.0 * m.dy), &ws[p], &wc[p]);
+        c[p] = 1.0;
+        s[p] = 0.0;
     }
-    if (valid) part[m.part0 + static_cast<int64_t>(cb) * m.K + k] = make_double2(re, im);
+    Acc R[kPT][kCT], J[kPT][kCT];
+#pragma unroll
+    for (int p = 0; p < kPT; ++p)
+#pragma unroll
+        for (int t = 0; t < kCT; ++t) R[p][t] = J[p][t] = Acc{0.0, 0.0, 0.0, 0.0};
+
+    const double* f = fold + m.fold0 + (static_cast<int64_t>(cb) * kCT * nq + q0) * 128 + lane;
+    const int64_t tile = static_cast<int64_t>(nq) * 128;
+    const double half = 0.5 * static_cast<double>(m.ny);
+    double S[kCT], D[kCT];
+#pragma unroll
+    for (int t = 0; t < kCT; ++t) {
+        S[t] = t < ct ? f[t * tile] : 0.0;
+        D[t] = t < ct ? f[t * tile + 64] : 0.0;
+    }
+    for (int32_t q = q0; q < q1; ++q) {
+        if (((q - q0) & (kReseed - 1)) == 0) {
+#pragma unroll
+            for (int p = 0; p < kPT; ++p)
+                dm::sincos(tv[p] * ((static_cast<double>(4 * q + r) + 0.5 - half) * m.dy), &s[p], &c[p]);
+        }
+        // the next quad's loads stay in flight under this quad's products
+        double Sn[kCT], Dn[kCT];
+        f += q + 1 < q1 ? 128 : 0;
+#pragma unroll
+        for (int t = 0; t < kCT; ++t) {
+            Sn[t] = t < ct ? f[t * tile] : 0.0;
+            Dn[t] = t < ct ? f[t * tile + 64] : 0.0;
+        }
+#pragma unroll
+        for (int p = 0; p < kPT; ++p)
+#pragma unroll
+            for (int t = 0; t < kCT; ++t) {
+                R[p][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[p], S[t], R[p][t], 0, 0, 0);
+                J[p][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(s[p], D[t], J[p][t], 0, 0, 0);
+            }
+#pragma unroll
+        for (int p = 0; p < kPT; ++p) {
+            const double cn = c[p] * wc[p] - s[p] * ws[p];
+            s[p] = s[p] * wc[p] + c[p] * ws[p];
+            c[p] = cn;
+        }
+#pragma unroll
+        for (int t = 0; t < kCT; ++t) {
+            S[t] = Sn[t];
+            D[t] = Dn[t];
+        }
+    }
+    // Columns.  Element v of a result tile is point r + 4 v of the point tile
+    // at column i16 of the column tile.  (The phases above were taken at the
+    // first row of each pair, Y_c - a, so the accumulated sine has the other
+    // sign.)
+    const double Yc = m.y0 + half * m.dy;
+    const double X = m.x0 + (static_cast<double>(cb * 16 * kCT + i16) + 0.5) * m.dx;
+#pragma unroll
+    for (int p = 0; p < kPT; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int32_t k = k0 + 16 * p + r + 4 * v;
+            const double pu = k < K ? -kTwoPi * m.uv[2 * k] : 0.0;
+            const double pv = k < K ? -kTwoPi * m.uv[2 * k + 1] : 0.0;
+            double xs, xc, vs, vc, ys, yc;
+            dm::sincos(pu * X, &xs, &xc);
+            dm::sincos(pv * Yc, &ys, &yc);
+            dm::sincos(pu * (16.0 * m.dx), &vs, &vc);
+            double re = 0.0, im = 0.0;
+#pragma unroll
+            for (int t = 0; t < kCT; ++t) {
+                const double a = R[p][t][v], b = -J[p][t][v];
+                re += xc * a - xs * b;
+                im += xc * b + xs * a;
+                const double cn = xc * vc - xs * vs;
+                xs = xs * vc + xc * vs;
+                xc = cn;
+            }
+            for (int off = 1; off < 16; off <<= 1) {
+                re += __shfl_xor(re, off);
+                im += __shfl_xor(im, off);
+            }
+            if (i16 == 0 && k < K)
+                part[m.part0 + static_cast<int64_t>(cell) * K + k] =
+                    make_double2(re * yc - im * ys, re * ys + im * yc);
+        }
 }
 
-// Flux partials: block b of image i sums the contiguous slice b of its pixels
-// (a fixed order: thread-strided, then a tree) into fpart[i kFluxBlocks + b].
-__global__ __launch_bounds__(kVisThreads) void vis_flux_kernel(const VisImage* __restrict__ tab,
-                                                               double* __restrict__ fpart) {
+// V_k = dX dY sum over the work items' partials (index order), amp_k = |V_k| / |F|.
+__global__ __launch_bounds__(kVisThreads) void vis_finish_kernel(const VisImage* __restrict__ tab,
+                                                                 const double2* __restrict__ part,
+                                                                 const double* __restrict__ fpart) {
     __shared__ double sh[kVisThreads];
+    static_assert(kVisFluxBlocks == kVisThreads, "one flux partial per thread");
     const VisImage& m = tab[blockIdx.y];
-    const int64_t n = static_cast<int64_t>(m.nx) * m.ny;
-    const int64_t per = (n + kVisFluxBlocks - 1) / kVisFluxBlocks;
-    const int64_t lo = per * blockIdx.x;
-    const int64_t hi = lo + per < n ? lo + per : n;
-    double s = 0.0;
-    for (int64_t p = lo + threadIdx.x; p < hi; p += kVisThreads) s += m.I[p];
-    sh[threadIdx.x] = s;
+    sh[threadIdx.x] = fpart[blockIdx.y * kVisFluxBlocks + threadIdx.x];
     __syncthreads();
     for (int w = kVisThreads / 2; w > 0; w >>= 1) {
         if (static_cast<int>(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) fpart[blockIdx.y * kVisFluxBlocks + blockIdx.x] = sh[0];
-}
-
-// V_k = dX dY sum over column blocks (index order), amp_k = |V_k| / |F|.
-__global__ __launch_bounds__(kVisThreads) void vis_finish_kernel(const VisImage* __restrict__ tab,
-                                                                 const double2* __restrict__ part,
-                                                                 const double* __restrict__ fpart) {
-    const VisImage& m = tab[blockIdx.y];
     const int32_t k = static_cast<int32_t>(blockIdx.x) * kVisThreads + threadIdx.x;
     if (k >= m.K) return;
-    double f = 0.0;
-    for (int b = 0; b < kVisFluxBlocks; ++b) f += fpart[blockIdx.y * kVisFluxBlocks + b];
     const double dxdy = m.dx * m.dy;
-    f *= dxdy;
+    const double f = sh[0] * dxdy;
     double re = 0.0, im = 0.0;
-    for (int32_t cb = 0; cb < m.ncb; ++cb) {
-        const double2 p = part[m.part0 + static_cast<int64_t>(cb) * m.K + k];
+    const int32_t cells = m.ncb * m.nseg;
+#pragma unroll 8
+    for (int32_t i = 0; i < cells; ++i) {
+        const double2 p = part[m.part0 + static_cast<int64_t>(i) * m.K + k];
         re += p.x;
         im += p.y;
     }
@@ -230,58 +246,73 @@ __global__ __launch_bounds__(kVisThreads) void vis_finish_kernel(const VisImage*
     if (m.amp) m.amp[k] = sqrt(re * re + im * im) / fabs(f);
 }
 
-// Points on rings: uv[j n_angles + a] = q_j (cos phi_a, sin phi_a),
-// phi_a = 2 pi a / n_angles.
+// Points on rings: uv[j n_dirs + a] = q_j (cos phi_a, sin phi_a),
+// phi_a = 2 pi a / n_angles, a < n_dirs.
 __global__ void ring_points_kernel(const double* __restrict__ q, int32_t n_q, int32_t n_angles,
-                                   double* __restrict__ uv) {
+                                   int32_t n_dirs, double* __restrict__ uv) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= static_cast<int64_t>(n_q) * n_angles) return;
-    const int32_t j = static_cast<int32_t>(i / n_angles);
-    const int32_t a = static_cast<int32_t>(i - static_cast<int64_t>(j) * n_angles);
+    if (i >= static_cast<int64_t>(n_q) * n_dirs) return;
+    const int32_t j = static_cast<int32_t>(i / n_dirs);
+    const int32_t a = static_cast<int32_t>(i - static_cast<int64_t>(j) * n_dirs);
     double s, c;
     dm::sincos(kTwoPi * static_cast<double>(a) / static_cast<double>(n_angles), &s, &c);
     uv[2 * i] = q[j] * c;
     uv[2 * i + 1] = q[j] * s;
 }
 
-// avg[j] = mean over the ring's n_angles amplitudes (index order); cut[j] =
+// avg[j] = mean over the ring's n_dirs amplitudes (index order); cut[j] =
 // the amplitude at phi = 0, i.e. at (u, v) = (q_j, 0).
-__global__ void ring_average_kernel(const double* __restrict__ amp, int32_t n_q, int32_t n_angles,
+__global__ void ring_average_kernel(const double* __restrict__ amp, int32_t n_q, int32_t n_dirs,
                                     double* __restrict__ avg, double* __restrict__ cut) {
     const int32_t j = static_cast<int32_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (j >= n_q) return;
-    const double* a = amp + static_cast<int64_t>(j) * n_angles;
+    const double* a = amp + static_cast<int64_t>(j) * n_dirs;
     double s = 0.0;
-    for (int32_t i = 0; i < n_angles; ++i) s += a[i];
-    if (avg) avg[j] = s / static_cast<double>(n_angles);
+    for (int32_t i = 0; i < n_dirs; ++i) s += a[i];
+    if (avg) avg[j] = s / static_cast<double>(n_dirs);
     if (cut) cut[j] = a[0];
 }
 
 }  // namespace
 
-void vis_layout(VisImage* tab, int32_t n_img, int32_t* n_items, int64_t* n_part) {
-    int64_t items = 0, parts = 0;
+// The split of an image into work items: 32 points x 64 columns, and as many
+// row segments (of 32 quads = 256 image rows or more) as bring it to about
+// kVisWaves wavefronts, four per SIMD: an image of 1024^2 at 1024 points has
+// 512 pairs of point and column blocks, which alone would leave half of the
+// SIMDs without a wavefront.
+constexpr int64_t kVisWaves = 4096;
+
+void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold) {
+    int64_t items = 0, parts = 0, fold = 0;
     for (int32_t i = 0; i < n_img; ++i) {
         VisImage& m = tab[i];
-        m.nkg = (m.K + 63) / 64;
-        m.ncb = (m.nx + kVisCols - 1) / kVisCols;
+        m.nkg = (m.K + 16 * kPT - 1) / (16 * kPT);
+        m.nct = (m.nx + 15) / 16;
+        m.ncb = (m.nct + kCT - 1) / kCT;
+        m.nq = ((m.ny + 1) / 2 + 3) / 4;
+        const int64_t cells = static_cast<int64_t>(m.nkg) * m.ncb;
+        const int64_t want = (kVisWaves + cells - 1) / cells, most = (m.nq + 31) / 32;
+        m.nseg = static_cast<int32_t>(want < most ? want : most);
         m.item0 = static_cast<int32_t>(items);
         m.part0 = parts;
-        items += static_cast<int64_t>(m.nkg) * m.ncb;
-        parts += static_cast<int64_t>(m.ncb) * m.K;
+        m.fold0 = fold;
+        items += cells * m.nseg;
+        parts += static_cast<int64_t>(m.ncb) * m.nseg * m.K;
+        fold += static_cast<int64_t>(m.nct) * m.nq * 128;
     }
-    *n_items = static_cast<int32_t>(items);
+    *n_items = items;
     *n_part = parts;
+    *n_fold = fold;
 }
 
 hipError_t launch_visibility(const VisImage* d_tab, int32_t n_img, int32_t n_items, int32_t max_k,
-                             double2* part, double* fpart, hipStream_t stream) {
-    hipLaunchKernelGGL(vis_flux_kernel, dim3(kVisFluxBlocks, static_cast<unsigned>(n_img)),
-                       dim3(kVisThreads), 0, stream, d_tab, fpart);
+                             double2* part, double* fold, double* fpart, hipStream_t stream) {
+    hipLaunchKernelGGL(vis_fold_kernel, dim3(kVisFluxBlocks, static_cast<unsigned>(n_img)),
+                       dim3(kVisThreads), 0, stream, d_tab, fold, fpart);
     const int32_t per_block = kVisThreads / 64;
     hipLaunchKernelGGL(vis_partial_kernel,
-                       dim3(static_cast<unsigned>((n_items + per_block - 1) / per_block)),
-                       dim3(kVisThreads), 0, stream, d_tab, n_img, n_items, part);
+                       dim3((static_cast<unsigned>(n_items) + per_block - 1) / per_block),
+                       dim3(kVisThreads), 0, stream, d_tab, n_img, n_items, fold, part);
     hipLaunchKernelGGL(vis_finish_kernel,
                        dim3(static_cast<unsigned>((max_k + kVisThreads - 1) / kVisThreads),
                             static_cast<unsigned>(n_img)),
@@ -289,18 +320,18 @@ hipError_t launch_visibility(const VisImage* d_tab, int32_t n_img, int32_t n_ite
     return hipGetLastError();
 }
 
-hipError_t launch_ring_points(const double* q, int32_t n_q, int32_t n_angles, double* uv,
-                              hipStream_t stream) {
-    const int64_t n = static_cast<int64_t>(n_q) * n_angles;
+hipError_t launch_ring_points(const double* q, int32_t n_q, int32_t n_angles, int32_t n_dirs,
+                              double* uv, hipStream_t stream) {
+    const int64_t n = static_cast<int64_t>(n_q) * n_dirs;
     hipLaunchKernelGGL(ring_points_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256),
-                       0, stream, q, n_q, n_angles, uv);
+                       0, stream, q, n_q, n_angles, n_dirs, uv);
     return hipGetLastError();
 }
 
-hipError_t launch_ring_average(const double* amp, int32_t n_q, int32_t n_angles, double* avg,
+hipError_t launch_ring_average(const double* amp, int32_t n_q, int32_t n_dirs, double* avg,
                                double* cut, hipStream_t stream) {
     hipLaunchKernelGGL(ring_average_kernel, dim3(static_cast<unsigned>((n_q + 255) / 256)),
-                       dim3(256), 0, stream, amp, n_q, n_angles, avg, cut);
+                       dim3(256), 0, stream, amp, n_q, n_dirs, avg, cut);
     return hipGetLastError();
 }
 

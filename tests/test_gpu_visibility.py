@@ -144,3 +144,29 @@ def test_relative_deviation(rt, orc):
     qc = torch.stack([dc[k] for k in rt.DIAG_KEYS])
     delta = rt.relative_to_reference(qc, qk).cpu().numpy()
     assert np.array_equal(delta, orc.relative_to_reference(qc.cpu().numpy(), qk.cpu().numpy()))
+
+
+@pytest.mark.parametrize("nx,ny,K", [(1, 1, 1), (15, 8, 16), (16, 9, 17), (17, 7, 32), (63, 255, 33), (64, 256, 31),
+                                     (65, 258, 2), (130, 519, 48), (8, 1031, 64)])
+def test_tile_edges(rt, orc, nx, ny, K):
+    """Screens and point counts around the edges of the kernel's tiles (16
+    columns in blocks of 64, quads of folded rows in segments, 16 points in
+    groups of 32), rings with an odd and an even number of angles."""
+    import torch
+    say(f"[vis] tile edges {nx} x {ny}, {K} points")
+    img = W.image(nx=nx, ny=ny, x_min=-9, x_max=11, y_min=-8, y_max=7)
+    I = torch.tensor(ring_image(img, nx + ny), device="cuda")
+    uv = torch.tensor(W.uv_points(nx * ny, K), device="cuda")
+    vis = torch.empty(K, 2, dtype=torch.float64, device="cuda")
+    rt.rt_visibility_dft(I, rt.params_from(img), uv, vis=vis)
+    In = I.cpu().numpy()
+    V = orc.visibility(img, In, uv.cpu().numpy())
+    flux = In.sum() * (20.0 / nx) * (15.0 / ny)
+    got = vis.cpu().numpy()
+    assert np.abs(got[:, 0] + 1j * got[:, 1] - V).max() <= TOL * flux
+    q = np.linspace(0.0, 0.4, 3)
+    for n_angles in (1, 2, 7, 12):
+        avg, cut = rt.visibility_rings(img, I, q, n_angles)
+        a, c = orc.visibility_rings(img, In, q, n_angles)
+        assert np.abs(avg.cpu().numpy() - a).max() <= TOL
+        assert np.abs(cut.cpu().numpy() - c).max() <= TOL
