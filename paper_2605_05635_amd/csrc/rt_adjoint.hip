@@ -52,10 +52,11 @@ __device__ __forceinline__ void add_wave_totals(uint32_t a, uint32_t b,
 
 // Pass 1.
 template <int METRIC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void vjp_forward_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void vjp_forward_kernel(
     ImageConst c, const double* __restrict__ dl_dI, int32_t slots, double* __restrict__ ckpt,
     int32_t* __restrict__ count, int32_t* __restrict__ kseg, unsigned long long* counters,
     unsigned long long* queue, LaunchShape shape) {
+    const fn::Pinned fns = fn::pin<METRIC>();
     const Hot k = hot_of(c);
     const OutPtrs none{};
     Ray r;
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     auto claim = [&]() { return claim_screen(shape, c.nx, c.ny, queue, next, end, tc); };
     auto take = [&](int64_t ordinal) {
         const int64_t pix = claimed_pixel(shape, c.nx, c.ny, tc, ordinal);
-        start_ray<METRIC>(c, k, pix, r);
+        start_ray<METRIC>(c, k, pix, r, fns);
         acc = 0;
         last = -1;
         K = kVjpSeg;
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             bool done = !live;
             if (live) {
                 const int32_t n0 = r.ncross;
-                const int32_t st = attempt<METRIC>(k, none, c.n_pix, r);
+                const int32_t st = attempt<METRIC>(k, none, c.n_pix, r, StageNone{}, fns);
                 if (st != RAY_STEP_LIMIT && r.after_reject == 0) {   // accepted
                     if (r.ncross != n0 && n0 < 3) {
                         const double Rc = n0 == 0 ? r.rc[0] : (n0 == 1 ? r.rc[1] : r.rc[2]);
@@ -184,13 +185,15 @@ __global__ __launch_bounds__(kBlock) void vjp_backward_kernel(
         if (__ballot(active) == 0ull) break;
         if (active && !fwd && n_rec == 0) active = false;   // an empty ray
         // Recompute: the lanes with a chunk to fill run attempts, recording the
-        // accepted steps rec_lo..rec_hi-1 of their segment.
+        // accepted steps rec_lo..rec_hi-1 of their segment.  (The coefficients are
+        // pinned for this phase only: the reversal needs the registers.)
+        const fn::Pinned fns = fn::pin<METRIC>();
         while (__ballot(active && fwd) != 0ull) {
             if (active && fwd) {
                 double* slot = buf + n_rec * kRecDoubles;
                 const double x0 = r.y[1], x1 = r.y[2], x2 = r.y[4], x3 = r.y[5], h = r.h;
                 const int32_t n0 = r.ncross;
-                const int32_t st = attempt<METRIC>(k, none, c.n_pix, r, vjp::TapeStages{slot});
+                const int32_t st = attempt<METRIC>(k, none, c.n_pix, r, vjp::TapeStages{slot}, fns);
                 if (st != RAY_STEP_LIMIT && r.after_reject == 0) {   // accepted
                     if (acc >= rec_lo) {
                         const bool crossed = r.ncross != n0 && n0 < 3;

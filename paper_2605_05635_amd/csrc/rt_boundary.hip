@@ -18,9 +18,9 @@ using namespace ray;
 
 constexpr int kMaxPasses = 64;
 
-// Register-allocated like the trace kernel (three waves per SIMD).
+// Register-allocated like the trace kernel.
 template <int METRIC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void boundary_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void boundary_kernel(
     ImageConst c, const double* __restrict__ dirs, int32_t n, int32_t S, double b_lo, double b_hi,
     double b_tol, double* __restrict__ out, int32_t* __restrict__ status,
     int64_t* __restrict__ attempts) {
@@ -30,6 +30,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const int grp = lane / S, sl = lane - grp * S;
     const int64_t dir = wave * G + grp;
     const unsigned long long gmask = S == 64 ? ~0ull : ((1ull << S) - 1ull);
+    const fn::Pinned fns = fn::pin<METRIC>();
     const Hot k = hot_of(c);
     const OutPtrs none{};    // no per-pixel outputs
     const bool mine = dir < n;
@@ -59,12 +60,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         }
         active = pass >= 0 || sl < 2;
         escaped = false;
-        if (active) start_ray_dir<METRIC>(c, k, screen_dir_xy(c, b * ux, b * uy), 0, r);
+        if (active) start_ray_dir<METRIC>(c, k, screen_dir_xy(c, b * ux, b * uy), 0, r, fns);
     };
     if (!done) start_pass();
     while (__ballot(!done) != 0ull) {
         if (active) {
-            const int32_t st = attempt<METRIC>(k, none, 0, r);
+            const int32_t st = attempt<METRIC>(k, none, 0, r, StageNone{}, fns);
             if (st != 0) {
                 active = false;
                 escaped = st == RAY_ESCAPED;

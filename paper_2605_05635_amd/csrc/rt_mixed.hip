@@ -84,13 +84,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 
 // A continued ray that reaches its second crossing is traced again from the
 // screen as well (and counted in counters[1]), so that every ray with two
-// crossings has its binary64 outputs.  Register-allocated for three waves per
-// SIMD, as the binary64 trace kernel: the pass is short (a third of the rays)
-// and ends on its longest rays, so it needs every wave it can keep resident.
+// crossings has its binary64 outputs.  Coefficients
+// pinned at two waves per SIMD, as the binary64 trace kernel (3.9 -> 3.2 ms for
+// the 327 k rays of the cored-NFW 1024^2 screen).
 template <int METRIC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void resume_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void resume_kernel(
     ImageConst c, OutPtrs o, const double* __restrict__ records, unsigned int* counters,
     unsigned long long* queue, int32_t chunk) {
+    const fn::Pinned fns = fn::pin<METRIC>();
     const Hot k = hot_of(c);
     const int64_t total = counters[0];
     Ray r;
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     auto claim = [&]() { return claim_chunk(queue, chunk, total, next, end); };
     auto take = [&](int64_t e) {
         const double* rec = records + e * kRecord;
-        load_record<METRIC>(c, k, rec, r);
+        load_record<METRIC>(c, k, rec, r, fns);
         fresh = rec[18] != 0.0;
     };
     uint32_t tried = 0;   // this lane's binary64 step attempts
@@ -109,9 +110,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         if (__ballot(active) == 0ull) break;
         if (active) {
             ++tried;
-            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r);
+            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r, StageNone{}, fns);
             if (!fresh && r.ncross >= kRerunCrossings) {
-                start_ray<METRIC>(c, k, r.pix, r);
+                start_ray<METRIC>(c, k, r.pix, r, fns);
                 fresh = true;
                 atomicAdd(&counters[1], 1u);
             } else if (st != 0) {

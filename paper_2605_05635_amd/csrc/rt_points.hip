@@ -20,21 +20,22 @@ constexpr int32_t kPointChunk = 64;   // points per work-queue claim (one wavefr
 // starting from (X_i, Y_i) and recorded as "pixel" i; its epilogue writes the
 // NaN records past min(N_cross, 3) (no pass after it but the emission).
 template <int METRIC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void trace_points_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void trace_points_kernel(
     ImageConst c, const double* __restrict__ xy, OutPtrs o, unsigned long long* queue) {
+    const fn::Pinned fns = fn::pin<METRIC>();
     const Hot k = hot_of(c);
     Ray r;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;
     auto claim = [&]() { return claim_chunk(queue, kPointChunk, c.n_pix, next, end); };
     auto take = [&](int64_t i) {
-        start_ray_dir<METRIC>(c, k, screen_dir_xy(c, xy[2 * i], xy[2 * i + 1]), i, r);
+        start_ray_dir<METRIC>(c, k, screen_dir_xy(c, xy[2 * i], xy[2 * i + 1]), i, r, fns);
     };
     for (;;) {
         if (!exhausted) refill(active, exhausted, next, end, claim, take);
         if (__ballot(active) == 0ull) break;
         if (active) {
-            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r);
+            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r, StageNone{}, fns);
             if (st != 0) {
                 finish_ray<true>(c, o, r, st);
                 active = false;

@@ -10,6 +10,7 @@
 
 #include "rt_device.h"
 #include "rt_dual.h"
+#include "rt_functions.h"
 #include "rt_kernels.h"
 #include "rt_math.h"
 
@@ -82,21 +83,23 @@ __host__ __device__ __forceinline__ Hot hot_of(const ImageConst& c) {
 //   dp_R/dl = -dH/dR = (N R/Sigma - dN/dR / 2) / Sigma                  (61)
 //   dp_th/dl= -dH/dth = cos/Sigma [W (l/sin^2 + chi E) - chi^2 sin N/Sigma]  (62)
 // The N dSigma terms keep the full derivative of H off the constraint shell.
-// chiE and chiL are chi E and chi l, constants of the ray.
-template <int METRIC, class K, class S>
+// chiE and chiL are chi E and chi l, constants of the ray; T is where sin, cos
+// and the mass function come from (rt_functions.h).
+template <int METRIC, class K, class S, class T = fn::Direct>
 __host__ __device__ __forceinline__ void rhs_c(const K& k, const S& E, const S& L, const S& chiE,
                                               const S& chiL, const S& R, const S& th,
-                                              const S& pR, const S& pth, S d[6]) {
-    const S half(0.5), two(2.0), four(4.0);
-    S s, co;
-    dm::sincos(th, &s, &co);
+                                              const S& pR, const S& pth, S d[6],
+                                              const T& tb = T{}) {
+    const S half(0.5), two(2.0);
+    S s, co;   // up to a common sign, which every product below cancels
+    fn::sincos(tb, th, &s, &co);
     S F, dF;
-    mass_function<METRIC>(k, R, F, dF);
+    fn::mass_function<METRIC>(tb, k, R, F, dF);
     const S R2 = R * R;
     const S R2c = R2 + k.chi2;
     const S Sig = R2 + k.chi2 * co * co;
     const S Del = R2c - F;
-    const S dDel = two * R - dF;
+    const S hDel = R - half * dF;   // half of dDelta/dR
     // 1/Sigma, 1/Delta and 1/sin(theta) from one reciprocal of their product
     const S SD = Sig * Del;
     const S inv = rcp(SD * s);
@@ -109,22 +112,22 @@ __host__ __device__ __forceinline__ void rhs_c(const K& k, const S& E, const S& 
     const S Lis2 = L * is * is;
     const S W = L * is - chiE * s;
     const S N = Del * pR * pR + pth * pth - P * PiD + W * W;
-    const S dN = dDel * (pR * pR + PiD * PiD) - four * R * E * PiD;
+    const S hdN = hDel * (pR * pR + PiD * PiD) - two * R * E * PiD;   // half of dN/dR
     d[0] = (PiD * R2c + k.chi * (L - chiE * s * s)) * iS;
     d[1] = Del * pR * iS;
     d[2] = pth * iS;
     d[3] = (k.chi * PiD + Lis2 - chiE) * iS;
     const S NiS = N * iS;
-    d[4] = (R * NiS - half * dN) * iS;
+    d[4] = (R * NiS - hdN) * iS;
     d[5] = co * iS * (W * (Lis2 + chiE) - k.chi2 * s * NiS);
 }
 
 // The same, forming chi E and chi l here (callers that evaluate many steps of
 // one ray pass them in, formed once).
-template <int METRIC, class K, class S>
+template <int METRIC, class K, class S, class T = fn::Direct>
 __host__ __device__ __forceinline__ void rhs(const K& k, const S& E, const S& L, const S& R, const S& th,
-                                    const S& pR, const S& pth, S d[6]) {
-    rhs_c<METRIC>(k, E, L, S(k.chi * E), S(k.chi * L), R, th, pR, pth, d);
+                                    const S& pR, const S& pth, S d[6], const T& tb = T{}) {
+    rhs_c<METRIC>(k, E, L, S(k.chi * E), S(k.chi * L), R, th, pR, pth, d, tb);
 }
 
 // ------------------------------------------------ Dormand-Prince 5(4) tableau
@@ -307,9 +310,10 @@ __host__ __device__ __forceinline__ void photon_constants(const ImageConst& c, c
 }
 
 // A ray from screen direction n, recorded as pixel pix.
-template <int METRIC>
+template <int METRIC, class T = fn::Direct>
 __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, const Hot& k,
-                                                       const ScreenDir& n, int64_t pix, Ray& r) {
+                                                       const ScreenDir& n, int64_t pix, Ray& r,
+                                                       const T& tb = T{}) {
     double E, L;
     photon_constants(c, n, E, L);
     set_constants(k.chi, E, L, r);
@@ -319,7 +323,7 @@ __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, cons
     r.y[3] = 0.0;
     r.y[4] = c.obs_sq_gRR * n.nR;
     r.y[5] = c.obs_sq_gthth * n.nth;
-    rhs<METRIC>(k, r.E, r.L, r.y[1], r.y[2], r.y[4], r.y[5], r.k1);
+    rhs<METRIC>(k, r.E, r.L, r.y[1], r.y[2], r.y[4], r.y[5], r.k1, tb);
     r.h = c.h0;
     r.lam = 0.0;
     r.last_cross = -INFINITY;
@@ -330,9 +334,10 @@ __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, cons
     r.pix = pix;
 }
 
-template <int METRIC>
-__host__ __device__ __forceinline__ void start_ray(const ImageConst& c, const Hot& k, int64_t pix, Ray& r) {
-    start_ray_dir<METRIC>(c, k, screen_dir(c, pix), pix, r);
+template <int METRIC, class T = fn::Direct>
+__host__ __device__ __forceinline__ void start_ray(const ImageConst& c, const Hot& k, int64_t pix, Ray& r,
+                                                   const T& tb = T{}) {
+    start_ray_dir<METRIC>(c, k, screen_dir(c, pix), pix, r, tb);
 }
 
 // A pixel as its index and its column and row.
@@ -341,10 +346,10 @@ struct Pixel {
     int32_t ix, iy;
 };
 
-template <int METRIC>
+template <int METRIC, class T = fn::Direct>
 __host__ __device__ __forceinline__ void start_ray(const ImageConst& c, const Hot& k, const Pixel& px,
-                                                   Ray& r) {
-    start_ray_dir<METRIC>(c, k, screen_dir_ij(c, px.ix, px.iy), px.pix, r);
+                                                   Ray& r, const T& tb = T{}) {
+    start_ray_dir<METRIC>(c, k, screen_dir_ij(c, px.ix, px.iy), px.pix, r, tb);
 }
 
 // Equatorial passage of a step from theta0 to theta1 (Sec. 3.3).
@@ -515,9 +520,9 @@ struct StageNone {
 
 // THICK: the thick disc's intensity as a seventh component (dI/dlambda =
 // thick_source, no feedback), in the error norm with the other six.
-template <int METRIC, class Sink = StageNone, bool THICK = false>
+template <int METRIC, class Sink = StageNone, bool THICK = false, class T = fn::Direct>
 __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs& o, int64_t n_pix,
-                                                    Ray& r, Sink sink = Sink{}) {
+                                                    Ray& r, Sink sink = Sink{}, const T& tb = T{}) {
     if (r.attempts >= k.max_attempts) return RAY_STEP_LIMIT;
     ++r.attempts;
     const double h = r.h;
@@ -544,7 +549,7 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     }
 #define RT_STAGE(expr, out)                                                      \
     for (int i = 0; i < 6; ++i) t[i] = r.y[i] + h * (expr);                       \
-    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, t[1], t[2], t[4], t[5], out);
+    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, t[1], t[2], t[4], t[5], out, tb);
 #define RT_ACC(bb, ee, dd, kv)                                                   \
     for (int i = 0; i < 6; ++i) {                                                \
         ab[i] += bb * kv[i];                                                     \
@@ -574,7 +579,7 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
 #undef RT_ACC_I
     double yn[6];
     for (int i = 0; i < 6; ++i) yn[i] = r.y[i] + h * ab[i];
-    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, yn[1], yn[2], yn[4], yn[5], kk);   // k7 (first-same-as-last)
+    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, yn[1], yn[2], yn[4], yn[5], kk, tb);   // k7 (first-same-as-last)
     double acc = 0.0;
     for (int i = 0; i < 6; ++i) {
         ae[i] += e7 * kk[i];

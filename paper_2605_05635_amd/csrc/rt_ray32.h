@@ -269,12 +269,12 @@ __device__ __forceinline__ void store_rerun(double* rec, int64_t pix) {
     rec[18] = 1.0;
 }
 
-template <int METRIC>
+template <int METRIC, class T = fn::Direct>
 __device__ __forceinline__ void load_record(const ImageConst& c, const Hot& k64, const double* rec,
-                                            Ray& w) {
+                                            Ray& w, const T& tb = T{}) {
     const int64_t pix = static_cast<int64_t>(rec[17]);
     if (rec[18] != 0.0) {
-        start_ray<METRIC>(c, k64, pix, w);
+        start_ray<METRIC>(c, k64, pix, w, tb);
         return;
     }
     for (int i = 0; i < 6; ++i) w.y[i] = rec[i];
@@ -289,7 +289,7 @@ __device__ __forceinline__ void load_record(const ImageConst& c, const Hot& k64,
     w.ncross = static_cast<int32_t>(rec[15]);
     w.after_reject = static_cast<int32_t>(rec[16]);
     w.pix = pix;
-    rhs<METRIC>(k64, w.E, w.L, w.y[1], w.y[2], w.y[4], w.y[5], w.k1);
+    rhs<METRIC>(k64, w.E, w.L, w.y[1], w.y[2], w.y[4], w.y[5], w.k1, tb);
 }
 
 }  // namespace ray32

@@ -27,15 +27,12 @@ namespace {
 
 using namespace ray;
 
-// The register allocation aims at three waves per SIMD (at most 168 VGPRs;
-// the cored NFW spills three values): measured 5-10 % faster than two.
-constexpr int kTraceWaves = 3;
-
-
-// Persistent trace kernel for one image (pixels handed out as shape says).
+// Persistent trace kernel for one image (pixels handed out as shape says), two
+// wavefronts per SIMD with the coefficients pinned (rt_functions.h).
 template <int METRIC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kTraceWaves, 8))) void trace_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void trace_kernel(
     ImageConst c, OutPtrs o, unsigned long long* queue, LaunchShape shape) {
+    const fn::Pinned fns = fn::pin<METRIC>();
     const Hot k = hot_of(c);
     Ray r;
     bool active = false, exhausted = false;
@@ -43,13 +40,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kTraceWa
     TileClaim tc{0, 0, 1, 1.0f};
     auto claim = [&]() { return claim_screen(shape, c.nx, c.ny, queue, next, end, tc); };
     auto take = [&](int64_t ordinal) {
-        start_ray<METRIC>(c, k, claimed(shape, c.nx, c.ny, tc, ordinal), r);
+        start_ray<METRIC>(c, k, claimed(shape, c.nx, c.ny, tc, ordinal), r, fns);
     };
     for (;;) {
         if (!exhausted) refill(active, exhausted, next, end, claim, take);
         if (__ballot(active) == 0ull) break;
         if (active) {
-            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r);
+            const int32_t st = attempt<METRIC>(k, o, c.n_pix, r, StageNone{}, fns);
             if (st != 0) {
                 finish_ray<false>(c, o, r, st);
                 active = false;
@@ -62,9 +59,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kTraceWa
 // copied into LDS once per workgroup; the work queue enumerates chunks of all
 // images (images ordered by metric, so a wavefront's lanes share a metric
 // except at the two metric boundaries).  Each lane keeps its image index and
-// the step-loop constants of that image in registers.  Register-allocated for
-// three waves per SIMD (167 VGPRs, 21 values spilled): 5 % faster than two.
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void trace_batch_kernel(
+// the step-loop constants of that image in registers.  The
+// coefficients of sine, cosine and the cored NFW are pinned (rt_functions.h;
+// with the Einasto exponential's too, 38 registers spill): 256 VGPRs, no
+// spills, where three wavefronts per SIMD spilled 21 values.  12 images of
+// 2.5 M rays: 17.2 -> 15.4 ms.
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void trace_batch_kernel(
     const ImageConst* __restrict__ table, const OutPtrs* __restrict__ outs,
     const int64_t* __restrict__ chunk_start, int32_t n_images, unsigned long long* queue,
     LaunchShape shape) {
@@ -81,6 +81,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     __syncthreads();
     const int64_t total_chunks = lcs[n_images];
 
+    const fn::Pinned fns = fn::pin<fn::kAll>();
     Ray r;
     Hot k{};
     int32_t img = 0, metric = KERR;
@@ -114,10 +115,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         px.pix = tile_pixel(ordinal, c.nx, c.ny, shape.tile_w, shape.tile_h, FpQuotient{});
         px.iy = quotient(static_cast<int32_t>(px.pix), c.nx);
         px.ix = static_cast<int32_t>(px.pix) - px.iy * c.nx;
-        if (metric == CNFW_NEAR) start_ray<CNFW_NEAR>(c, k, px, r);
-        else if (metric == CNFW) start_ray<CNFW>(c, k, px, r);
-        else if (metric == EINASTO) start_ray<EINASTO>(c, k, px, r);
-        else start_ray<KERR>(c, k, px, r);
+        if (metric == CNFW_NEAR) start_ray<CNFW_NEAR>(c, k, px, r, fns);
+        else if (metric == CNFW) start_ray<CNFW>(c, k, px, r, fns);
+        else if (metric == EINASTO) start_ray<EINASTO>(c, k, px, r, fns);
+        else start_ray<KERR>(c, k, px, r, fns);
     };
     for (;;) {
         if (!exhausted) refill(active, exhausted, next, end, claim, take);
@@ -126,10 +127,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             const OutPtrs& o = outs[img];
             const int64_t n_pix = lt[img].n_pix;
             int32_t st;
-            if (metric == CNFW_NEAR) st = attempt<CNFW_NEAR>(k, o, n_pix, r);
-            else if (metric == CNFW) st = attempt<CNFW>(k, o, n_pix, r);
-            else if (metric == EINASTO) st = attempt<EINASTO>(k, o, n_pix, r);
-            else st = attempt<KERR>(k, o, n_pix, r);
+            if (metric == CNFW_NEAR) st = attempt<CNFW_NEAR>(k, o, n_pix, r, StageNone{}, fns);
+            else if (metric == CNFW) st = attempt<CNFW>(k, o, n_pix, r, StageNone{}, fns);
+            else if (metric == EINASTO) st = attempt<EINASTO>(k, o, n_pix, r, StageNone{}, fns);
+            else st = attempt<KERR>(k, o, n_pix, r, StageNone{}, fns);
             if (st != 0) {
                 finish_ray<false>(lt[img], o, r, st);
                 active = false;

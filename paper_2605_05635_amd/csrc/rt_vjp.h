@@ -79,10 +79,10 @@ __host__ __device__ __forceinline__ void store_checkpoint(double* slot, const Ra
 
 // Restores the checkpoint `slot` into r (pixel pix, constants E, l) for the
 // metric's right-hand side; returns its accepted-step index.
-template <int METRIC>
+template <int METRIC, class T = fn::Direct>
 __host__ __device__ __forceinline__ int32_t load_checkpoint(const double* slot, const Hot& k,
                                                             double E, double L, int64_t pix,
-                                                            Ray& r) {
+                                                            Ray& r, const T& tb = T{}) {
     const double2* q = reinterpret_cast<const double2*>(slot);
     const double2 a = q[0], b = q[1], c = q[2], d = q[3], e = q[4], f = q[5], g = q[6],
                   h = q[7];
@@ -103,7 +103,7 @@ __host__ __device__ __forceinline__ int32_t load_checkpoint(const double* slot, 
     r.ncross = static_cast<int32_t>(h.y);
     set_constants(k.chi, E, L, r);
     r.pix = pix;
-    rhs<METRIC>(k, E, L, r.y[1], r.y[2], r.y[4], r.y[5], r.k1);
+    rhs<METRIC>(k, E, L, r.y[1], r.y[2], r.y[4], r.y[5], r.k1, tb);
     return static_cast<int32_t>(g.y);
 }
 
