@@ -50,7 +50,8 @@ __host__ __device__ __forceinline__ void mass_function(const Direct&, const K& c
 
 // The coefficients of dm::sincos_pi, dm::log_kernel, dm::expm1_near and dm::exp
 // (highest degree first) with their reduction constants.
-struct Pinned {
+template <bool SCALAR>
+struct PinnedSet {
     double s[8] = {2.7314447669863206e-15, -7.643970296798566e-13, 1.6058977312464087e-10,
                    -2.5052107616996182e-08, 2.7557319219163234e-06, -0.00019841269841254974,
                    0.008333333333333316, -0.16666666666666666};
@@ -70,13 +71,19 @@ struct Pinned {
                      0.1666666666666667};
     double ln2_hi = dm::kLn2Hi, ln2_lo = dm::kLn2Lo, inv_ln2 = dm::kInvLn2;
 };
+using Pinned = PinnedSet<false>;
+// The thick disc's kernel has registers for sine's and cosine's coefficients
+// only; those of its exponentials and logarithm go through scalar registers at
+// each use (left to itself the compiler builds them in vector registers, two
+// vector moves a coefficient).
+using PinnedThick = PinnedSet<true>;
 
 // The coefficients as the kernel of a metric holds them: in vector registers,
 // opaque to the compiler so that it cannot turn them back into literals.
 constexpr int kAll = -1;   // every metric's coefficients (the batched kernel)
-template <int METRIC>
-__device__ __forceinline__ Pinned pin() {
-    Pinned p;
+template <int METRIC, bool SCALAR = false>
+__device__ __forceinline__ PinnedSet<SCALAR> pin() {
+    PinnedSet<SCALAR> p;
 #if defined(__HIP_DEVICE_COMPILE__)
     auto hold = [](double& x) { asm volatile("" : "+v"(x)); };
 #pragma unroll
@@ -88,7 +95,7 @@ __device__ __forceinline__ Pinned pin() {
     hold(p.inv_pi);
     hold(p.pi_hi);
     hold(p.pi_mid);
-    if constexpr (METRIC == CNFW_NEAR || METRIC == kAll) {
+    if constexpr (!SCALAR && (METRIC == CNFW_NEAR || METRIC == kAll)) {
 #pragma unroll
         for (int i = 0; i < 7; ++i) hold(p.lw[i]);
 #pragma unroll
@@ -96,7 +103,7 @@ __device__ __forceinline__ Pinned pin() {
         hold(p.ln2_hi);
         hold(p.ln2_lo);
     }
-    if constexpr (METRIC == EINASTO) {
+    if constexpr (!SCALAR && METRIC == EINASTO) {
 #pragma unroll
         for (int i = 0; i < 10; ++i) hold(p.ex[i]);
         hold(p.ln2_hi);
@@ -107,35 +114,89 @@ __device__ __forceinline__ Pinned pin() {
     return p;
 }
 
-template <int N>
+template <bool SCALAR = false, int N>
 __host__ __device__ __forceinline__ double horner(const double (&c)[N], double x) {
     double p = c[0];
 #pragma unroll
-    for (int i = 1; i < N; ++i) p = fma(p, x, c[i]);
+    for (int i = 1; i < N; ++i) {
+        double ci = c[i];
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (SCALAR) asm("" : "+s"(ci) : "v"(p));
+#endif
+        p = fma(p, x, ci);
+    }
     return p;
 }
 
-__host__ __device__ __forceinline__ void sincos(const Pinned& q, const double& x, double* s_out,
-                                                double* c_out) {
+template <bool S>
+__host__ __device__ __forceinline__ int32_t sincos_pi(const PinnedSet<S>& q, double x, double* s_out,
+                                                      double* c_out) {
     const dm::NearestInt n = dm::nearest_int(x, q.inv_pi);
     double r = fma(-n.k, q.pi_hi, x);
     r = fma(-n.k, q.pi_mid, r);
     const double z = r * r;
     *s_out = fma(r * z, horner(q.s, z), r);
     *c_out = fma(z, horner(q.c, z), 1.0);
+    return n.i;
 }
 
-template <int METRIC, class K>
-__host__ __device__ __forceinline__ void mass_function(const Pinned& q, const K& c, const double& R,
+template <bool S>
+__host__ __device__ __forceinline__ void sincos(const PinnedSet<S>& q, const double& x, double* s_out,
+                                                double* c_out) {
+    sincos_pi(q, x, s_out, c_out);
+}
+
+// With their signs (the thick disc's source needs them).
+__host__ __device__ __forceinline__ void signed_sincos(const Direct&, double x, double* s_out,
+                                                       double* c_out) {
+    dm::sincos(x, s_out, c_out);
+}
+template <bool S>
+__host__ __device__ __forceinline__ void signed_sincos(const PinnedSet<S>& q, double x, double* s_out,
+                                                       double* c_out) {
+    const int32_t k = sincos_pi(q, x, s_out, c_out);
+    dm::flip_signs(k, s_out, c_out);
+}
+
+// e^x and log(1 + u), as dm::exp and dm::log1p.
+__host__ __device__ __forceinline__ double exp(const Direct&, double x) { return dm::exp(x); }
+__host__ __device__ __forceinline__ double log1p(const Direct&, double u) { return dm::log1p(u); }
+template <bool S>
+__host__ __device__ __forceinline__ double exp(const PinnedSet<S>& q, double x) {
+    const double xc = fmin(fmax(x, -760.0), 720.0);
+    const dm::NearestInt n = dm::nearest_int(xc, q.inv_ln2);
+    double r = fma(-n.k, q.ln2_hi, xc);
+    r = fma(-n.k, q.ln2_lo, r);
+    const double p = fma(horner<S>(q.ex, r), r, 0.5);
+    return ldexp(1.0 + fma(r * r, p, r), n.i);
+}
+template <bool S>
+__host__ __device__ __forceinline__ double log1p(const PinnedSet<S>& q, double u) {
+    const double v = 1.0 + u;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double corr = (u - (v - 1.0)) * __builtin_amdgcn_rcp(v);
+#else
+    const double corr = (u - (v - 1.0)) / v;
+#endif
+    int e;
+    double m = frexp(v, &e);
+    if (m < 0.70710678118654752) {
+        m *= 2.0;
+        e -= 1;
+    }
+    const double w = fma(m, 2.0, -2.0) * dm::recip(m + 1.0);
+    const double z = w * w;
+    const double logm = fma(w * z, horner<S>(q.lw, z), w);
+    const double de = static_cast<double>(e);
+    return fma(de, q.ln2_hi, logm + fma(de, q.ln2_lo, corr));
+}
+
+template <int METRIC, class K, bool S>
+__host__ __device__ __forceinline__ void mass_function(const PinnedSet<S>& q, const K& c, const double& R,
                                                        double& F, double& dF) {
     if constexpr (METRIC == EINASTO) {
         const double x = R * c.inv_lam;
-        const double xc = fmin(fmax(-x, -760.0), 720.0);
-        const dm::NearestInt n = dm::nearest_int(xc, q.inv_ln2);
-        double r = fma(-n.k, q.ln2_hi, xc);
-        r = fma(-n.k, q.ln2_lo, r);
-        const double p = fma(horner(q.ex, r), r, 0.5);
-        const double e = ldexp(1.0 + fma(r * r, p, r), n.i);
+        const double e = exp(q, -x);
         const double mu = 1.0 - e * (1.0 + x * (1.0 + 0.5 * x));
         const double dmu = 0.5 * e * x * x * c.inv_lam;
         F = 2.0 * R * mu;
@@ -149,11 +210,11 @@ __host__ __device__ __forceinline__ void mass_function(const Pinned& q, const K&
         const double iR = Rl * a, iRl = R * a;
         const double w = fma(s.m, 2.0, -2.0) * (d * inv);
         const double v = w * w;
-        const double lk = fma(w * v, horner(q.lw, v), w);
+        const double lk = fma(w * v, horner<S>(q.lw, v), w);
         const double lg = fma(s.e, q.ln2_hi, fma(s.e, q.ln2_lo, lk));
         const double ex = c.eta_lc * (iRl - 2.0 * iR * lg);
         const double dex = c.eta_lc * (2.0 * iR * (iR * lg - iRl) - iRl * iRl);
-        const double em1 = fma(ex * ex, fma(horner(q.en, ex), ex, 0.5), ex);
+        const double em1 = fma(ex * ex, fma(horner<S>(q.en, ex), ex, 0.5), ex);
         F = R * (2.0 - R * em1);
         dF = 2.0 - R * (2.0 * em1 + R * (em1 + 1.0) * dex);
     } else {

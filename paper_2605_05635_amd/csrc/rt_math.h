@@ -122,6 +122,25 @@ __host__ __device__ inline double rsqrt(double x) {
 #endif
 }
 
+// sqrt(x) for x = 0, x >= 2^-767 or +infinity: the compiler's correctly rounded
+// sequence (a Goldschmidt step from the hardware estimate of 1/sqrt, two
+// residual corrections) without the scaling that serves smaller arguments,
+// eight of its 22 instructions.
+__host__ __device__ inline double sqrt_normal(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return __builtin_amdgcn_class(x, 0x260) ? x : g;   // +-0, +infinity
+#else
+    return std::sqrt(x);
+#endif
+}
+
 // sin and cos of x, |x| < 3.2e6: x = k pi + r with |r| <= pi/2, so that
 // sin x = (-1)^k sin r and cos x = (-1)^k cos r.  Reducing by pi rather than
 // pi/2 leaves a sign flip of both results in place of the quadrant's swap and
@@ -165,13 +184,16 @@ __host__ __device__ inline int32_t sincos_pi(double x, double* s_out, double* c_
     return n.i;
 }
 
-__host__ __device__ inline void sincos(double x, double* s_out, double* c_out) {
-    double s, c;
-    const int32_t k = sincos_pi(x, &s, &c);
-    // (-1)^k as the sign bit of the high word
+// (*s, *c) times (-1)^k, as the sign bit of the high word.
+__host__ __device__ inline void flip_signs(int32_t k, double* s, double* c) {
     const uint64_t flip = static_cast<uint64_t>(static_cast<uint32_t>(k) << 31) << 32;
-    *s_out = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, s) ^ flip);
-    *c_out = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, c) ^ flip);
+    *s = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, *s) ^ flip);
+    *c = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, *c) ^ flip);
+}
+
+__host__ __device__ inline void sincos(double x, double* s_out, double* c_out) {
+    const int32_t k = sincos_pi(x, s_out, c_out);
+    flip_signs(k, s_out, c_out);
 }
 
 // e^r - 1 = r + r^2 E(r) for |r| <= ln(2)/2 + 1e-9: a polynomial kernel of

@@ -83,18 +83,15 @@ __host__ __device__ __forceinline__ Hot hot_of(const ImageConst& c) {
 //   dp_R/dl = -dH/dR = (N R/Sigma - dN/dR / 2) / Sigma                  (61)
 //   dp_th/dl= -dH/dth = cos/Sigma [W (l/sin^2 + chi E) - chi^2 sin N/Sigma]  (62)
 // The N dSigma terms keep the full derivative of H off the constraint shell.
-// chiE and chiL are chi E and chi l, constants of the ray; T is where sin, cos
-// and the mass function come from (rt_functions.h).
-template <int METRIC, class K, class S, class T = fn::Direct>
-__host__ __device__ __forceinline__ void rhs_c(const K& k, const S& E, const S& L, const S& chiE,
-                                              const S& chiL, const S& R, const S& th,
-                                              const S& pR, const S& pth, S d[6],
-                                              const T& tb = T{}) {
+// chiE and chiL are chi E and chi l, constants of the ray; s, co, F and dF the
+// sine and cosine of theta (up to a common sign, which every product below
+// cancels) and the mass function at R.
+template <class K, class S>
+__host__ __device__ __forceinline__ void rhs_at(const K& k, const S& E, const S& L, const S& chiE,
+                                                const S& chiL, const S& R, const S& pR,
+                                                const S& pth, const S& s, const S& co, const S& F,
+                                                const S& dF, S d[6]) {
     const S half(0.5), two(2.0);
-    S s, co;   // up to a common sign, which every product below cancels
-    fn::sincos(tb, th, &s, &co);
-    S F, dF;
-    fn::mass_function<METRIC>(tb, k, R, F, dF);
     const S R2 = R * R;
     const S R2c = R2 + k.chi2;
     const S Sig = R2 + k.chi2 * co * co;
@@ -120,6 +117,19 @@ __host__ __device__ __forceinline__ void rhs_c(const K& k, const S& E, const S& 
     const S NiS = N * iS;
     d[4] = (R * NiS - hdN) * iS;
     d[5] = co * iS * (W * (Lis2 + chiE) - k.chi2 * s * NiS);
+}
+
+// The same at (R, theta), with sine, cosine and mass function from T
+// (rt_functions.h).
+template <int METRIC, class K, class S, class T = fn::Direct>
+__host__ __device__ __forceinline__ void rhs_c(const K& k, const S& E, const S& L, const S& chiE,
+                                              const S& chiL, const S& R, const S& th,
+                                              const S& pR, const S& pth, S d[6],
+                                              const T& tb = T{}) {
+    S s, co, F, dF;
+    fn::sincos(tb, th, &s, &co);
+    fn::mass_function<METRIC>(tb, k, R, F, dF);
+    rhs_at(k, E, L, chiE, chiL, R, pR, pth, s, co, F, dF, d);
 }
 
 // The same, forming chi E and chi l here (callers that evaluate many steps of
@@ -447,7 +457,8 @@ __host__ __device__ __forceinline__ double crossing_root(const DenseComp& d, boo
 }
 
 // dI/dlambda = g^3 j of the thick disc (Sec. 5.1-5.2) at (R, theta) for a
-// photon (E, l) of unit observer-frame energy: the emissivity eq. (84) with
+// photon (E, l) of unit observer-frame energy, from s and co = sin and cos of
+// theta and the mass function at R: the emissivity eq. (84) with
 // j_0 = 1, rho = R sin(theta), z = R cos(theta), H = H_0 + h rho and the
 // window of the image (tapers of eqs. (85)-(86) or hard edges); the emitter
 // moves with the circular equatorial angular velocity of eq. (91) at the same
@@ -455,18 +466,17 @@ __host__ __device__ __forceinline__ double crossing_root(const DenseComp& d, boo
 // emission where that has no solution.  The quotients go through reciprocals
 // of their denominators (g^3 = A^(3/2) (1/den)^3).  The early returns stay:
 // a branch-free version kept more values live and spilled.
-template <int METRIC>
-__host__ __device__ inline double thick_source(const Hot& k, double R, double th, double E, double L) {
-    double s, co;
-    dm::sincos(th, &s, &co);
+template <class T>
+__host__ __device__ inline double thick_source(const Hot& k, double R, double s, double co, double F,
+                                               double dF, double E, double L, const T& tb) {
     const double rho = R * s, z = R * co;
     if (!(rho > 0.0)) return 0.0;
     double w;
     if (k.taper) {
         // (1 + tanh u)/2 = 1/(1 + e^{-2u}), (1 - tanh u)/2 = 1/(1 + e^{2u}): one
         // reciprocal of the product, 0 where it is infinite (far outside the edges)
-        const double p = (1.0 + dm::exp(-(rho - k.r_in) * k.tin)) *
-                         (1.0 + dm::exp((rho - k.r_out) * k.tout));
+        const double p = (1.0 + fn::exp(tb, -(rho - k.r_in) * k.tin)) *
+                         (1.0 + fn::exp(tb, (rho - k.r_out) * k.tout));
         w = p < INFINITY ? rcp(p) : 0.0;
     } else {
         w = (rho >= k.r_in && rho <= k.r_out) ? 1.0 : 0.0;
@@ -475,16 +485,14 @@ __host__ __device__ inline double thick_source(const Hot& k, double R, double th
     const double H = k.thick_h0 + k.thick_h * rho;
     const double zH = z * rcp(H);
     // the three factors of eq. (84) as one exponential
-    const double j = dm::exp(-k.emis_pow * dm::log1p(rho * k.inv_r_in - 1.0) -
+    const double j = fn::exp(tb, -k.emis_pow * fn::log1p(tb, rho * k.inv_r_in - 1.0) -
                              (rho - k.r_in) * k.inv_rs - 0.5 * zH * zH) *
                      w;
-    double F, dF;
-    mass_function<METRIC>(k, R, F, dF);
     const double iR = rcp(R);
     const double G = (dF - 2.0 * F * iR) * (iR * iR);   // d(F/R^2)/dR
     const double disc = -2.0 * R * G;
     if (!(disc >= 0.0)) return 0.0;
-    const double Om = (k.chi * G + sqrt(disc)) * rcp(2.0 * R + k.chi2 * G);
+    const double Om = (k.chi * G + dm::sqrt_normal(disc)) * rcp(2.0 * R + k.chi2 * G);
     const double FiS = F * rcp(R * R + k.chi2 * co * co);   // F/Sigma
     const double s2 = s * s;
     const double gTT = -(1.0 - FiS);
@@ -495,16 +503,19 @@ __host__ __device__ inline double thick_source(const Hot& k, double R, double th
     const double den = E - Om * L;
     if (!(den > 0.0)) return 0.0;
     const double id = rcp(den);
-    return A * sqrt(A) * (id * id * id) * j;
+    return A * dm::sqrt_normal(A) * (id * id * id) * j;
 }
 
 // A thick-disc ray: as start_ray, with I = 0 and its source at the start.
-template <int METRIC>
+template <int METRIC, class T>
 __host__ __device__ __forceinline__ void start_ray_thick(const ImageConst& c, const Hot& k, int64_t pix,
-                                                         Ray& r) {
-    start_ray<METRIC>(c, k, pix, r);
+                                                         Ray& r, const T& tb) {
+    start_ray<METRIC>(c, k, pix, r, tb);
+    double s, co, F, dF;
+    fn::signed_sincos(tb, r.y[2], &s, &co);
+    fn::mass_function<METRIC>(tb, k, r.y[1], F, dF);
     r.I = 0.0;
-    r.kI = thick_source<METRIC>(k, r.y[1], r.y[2], r.E, r.L);
+    r.kI = thick_source(k, r.y[1], s, co, F, dF, r.E, r.L, tb);
 }
 
 // One step attempt.  Returns 0 while the ray runs, else its final status.
@@ -539,17 +550,28 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
         abI = b1 * r.kI;
         aeI = e1 * r.kI;
     }
+    double s_ = 0.0, co_ = 0.0, F_ = 0.0, dF_ = 0.0;   // THICK: functions at the stage input t
+// The right-hand side at stage input x.  THICK forms sine, cosine and mass
+// function once for it and the source.
+#define RT_RHS(x, out)                                                           \
+    if constexpr (THICK) {                                                       \
+        fn::signed_sincos(tb, x[2], &s_, &co_);                                  \
+        fn::mass_function<METRIC>(tb, k, x[1], F_, dF_);                         \
+        rhs_at(k, r.E, r.L, r.chiE, r.chiL, x[1], x[4], x[5], s_, co_, F_, dF_, out); \
+    } else {                                                                     \
+        rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, x[1], x[2], x[4], x[5], out, tb); \
+    }
 // THICK: the source at the current stage input t (b_2 = e_2 = 0: stage 2
 // needs none)
 #define RT_ACC_I(bb, ee)                                                         \
     if constexpr (THICK) {                                                       \
-        const double kI_ = thick_source<METRIC>(k, t[1], t[2], r.E, r.L);        \
+        const double kI_ = thick_source(k, t[1], s_, co_, F_, dF_, r.E, r.L, tb); \
         abI += bb * kI_;                                                         \
         aeI += ee * kI_;                                                         \
     }
 #define RT_STAGE(expr, out)                                                      \
     for (int i = 0; i < 6; ++i) t[i] = r.y[i] + h * (expr);                       \
-    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, t[1], t[2], t[4], t[5], out, tb);
+    RT_RHS(t, out)
 #define RT_ACC(bb, ee, dd, kv)                                                   \
     for (int i = 0; i < 6; ++i) {                                                \
         ab[i] += bb * kv[i];                                                     \
@@ -579,7 +601,8 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
 #undef RT_ACC_I
     double yn[6];
     for (int i = 0; i < 6; ++i) yn[i] = r.y[i] + h * ab[i];
-    rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, yn[1], yn[2], yn[4], yn[5], kk, tb);   // k7 (first-same-as-last)
+    RT_RHS(yn, kk)   // k7 (first-same-as-last)
+#undef RT_RHS
     double acc = 0.0;
     for (int i = 0; i < 6; ++i) {
         ae[i] += e7 * kk[i];
@@ -590,7 +613,7 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     }
     double ynI = 0.0, kI7 = 0.0;
     if constexpr (THICK) {
-        kI7 = thick_source<METRIC>(k, yn[1], yn[2], r.E, r.L);
+        kI7 = thick_source(k, yn[1], s_, co_, F_, dF_, r.E, r.L, tb);
         aeI += e7 * kI7;
         ynI = r.I + h * abI;
         const double sc = k.atol + k.rtol * fmax(fabs(r.I), fabs(ynI));

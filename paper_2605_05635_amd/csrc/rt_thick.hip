@@ -22,9 +22,18 @@ __device__ __forceinline__ const ImageConst& reloaded_args() {
     return *q;
 }
 
+// Bound by its vector instructions (about 2,400 an attempt).  Of those a sixth
+// were moves that built polynomial coefficients in vector registers, and the
+// square roots' range scaling: sine's and cosine's coefficients are pinned, the
+// others taken through scalar registers (rt_functions.h, PinnedThick), and the
+// roots need no scaling (dm::sqrt_normal).  1024^2 cored NFW 12.66 -> 12.02 ms,
+// 64^2 3.01 -> 2.69, the same bits.  (All coefficients pinned: 48 registers
+// spilled.  The exponential's and logarithm's held in scalar registers over the
+// whole loop: 28 scalar registers spilled, 258 lane reads.)
 template <int METRIC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) void trace_thick_kernel(
     ImageConst c, OutPtrs o, unsigned long long* queue, LaunchShape shape) {
+    const fn::PinnedThick fns = fn::pin<METRIC, true>();
     Ray r;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;
@@ -35,13 +44,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
     };
     auto take = [&](int64_t ordinal) {
         const ImageConst& a = reloaded_args();
-        start_ray_thick<METRIC>(a, hot_of(a), claimed_pixel(shape, a.nx, a.ny, tc, ordinal), r);
+        start_ray_thick<METRIC>(a, hot_of(a), claimed_pixel(shape, a.nx, a.ny, tc, ordinal), r, fns);
     };
     for (;;) {
         if (!exhausted) refill(active, exhausted, next, end, claim, take);
         if (__ballot(active) == 0ull) break;
         if (active) {
-            const int32_t st = attempt<METRIC, StageNone, true>(hot_of(reloaded_args()), o, c.n_pix, r);
+            const int32_t st = attempt<METRIC, StageNone, true>(hot_of(reloaded_args()), o, c.n_pix, r,
+                                                                StageNone{}, fns);
             if (st != 0) {
                 finish_ray(reloaded_args(), o, r, st);
                 o.intensity[r.pix] = r.I;
