@@ -475,13 +475,15 @@ int trace_common(const rt_image_params* params, int32_t n_images, const rt_image
                                emission ? out[i].intensity : nullptr,
                                emission ? out[i].intensity_n : nullptr, out[i].attempts};
     // Binary64 images: one launch for a single image, else batches grouped by
-    // metric (stable), at most kMaxBatch per launch.  Mixed-precision images
+    // metric (stable), at most kMaxBatch per launch, the costliest metric first:
+    // the launch then drains on the shortest steps (Kerr's 675 vector
+    // instructions, against 844 Einasto and 995 cored NFW).  Mixed-precision images
     // run one by one after them.
     std::vector<int> order, mixed;
     for (int i = 0; i < n_images; ++i)
         (params[i].precision == RT_MIXED ? mixed : order).push_back(i);
     std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return consts[a].metric < consts[b].metric; });
+                     [&](int a, int b) { return consts[a].metric > consts[b].metric; });
     const int nf = static_cast<int>(order.size());
     const int n_launch = nf <= 1 ? nf : (nf + kMaxBatch - 1) / kMaxBatch;
 

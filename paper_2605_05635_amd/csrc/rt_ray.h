@@ -319,11 +319,24 @@ __host__ __device__ __forceinline__ void photon_constants(const ImageConst& c, c
     L = c.obs_sq_gphph * n.nph;
 }
 
-// A ray from screen direction n, recorded as pixel pix.
+// The functions of the right-hand side at the observer (R_o, theta_o): every ray
+// of an image starts there.
+struct AtObserver {
+    double s, co, F, dF;
+};
 template <int METRIC, class T = fn::Direct>
+__host__ __device__ __forceinline__ AtObserver at_observer(const ImageConst& c, const Hot& k,
+                                                           const T& tb = T{}) {
+    AtObserver a;
+    fn::sincos(tb, c.incl, &a.s, &a.co);
+    fn::mass_function<METRIC>(tb, k, c.r_obs, a.F, a.dF);
+    return a;
+}
+
+// A ray from screen direction n, recorded as pixel pix.
 __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, const Hot& k,
-                                                       const ScreenDir& n, int64_t pix, Ray& r,
-                                                       const T& tb = T{}) {
+                                                       const AtObserver& a, const ScreenDir& n,
+                                                       int64_t pix, Ray& r) {
     double E, L;
     photon_constants(c, n, E, L);
     set_constants(k.chi, E, L, r);
@@ -333,7 +346,7 @@ __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, cons
     r.y[3] = 0.0;
     r.y[4] = c.obs_sq_gRR * n.nR;
     r.y[5] = c.obs_sq_gthth * n.nth;
-    rhs<METRIC>(k, r.E, r.L, r.y[1], r.y[2], r.y[4], r.y[5], r.k1, tb);
+    rhs_at(k, r.E, r.L, r.chiE, r.chiL, r.y[1], r.y[4], r.y[5], a.s, a.co, a.F, a.dF, r.k1);
     r.h = c.h0;
     r.lam = 0.0;
     r.last_cross = -INFINITY;
@@ -342,6 +355,13 @@ __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, cons
     r.ncross = 0;
     r.after_reject = 0;
     r.pix = pix;
+}
+
+template <int METRIC, class T = fn::Direct>
+__host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, const Hot& k,
+                                                       const ScreenDir& n, int64_t pix, Ray& r,
+                                                       const T& tb = T{}) {
+    start_ray_dir(c, k, at_observer<METRIC>(c, k, tb), n, pix, r);
 }
 
 template <int METRIC, class T = fn::Direct>

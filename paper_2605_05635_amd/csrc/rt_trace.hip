@@ -70,7 +70,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     LaunchShape shape) {
     extern __shared__ unsigned char lds_raw[];
     ImageConst* lt = reinterpret_cast<ImageConst*>(lds_raw);
-    int64_t* lcs = reinterpret_cast<int64_t*>(lds_raw + sizeof(ImageConst) * n_images);
+    AtObserver* lobs = reinterpret_cast<AtObserver*>(lds_raw + sizeof(ImageConst) * n_images);
+    int64_t* lcs = reinterpret_cast<int64_t*>(lobs + n_images);
     {
         const int words = static_cast<int>(sizeof(ImageConst) / 8) * n_images;
         const uint64_t* src = reinterpret_cast<const uint64_t*>(table);
@@ -80,6 +81,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     __syncthreads();
     const int64_t total_chunks = lcs[n_images];
+    // what the first right-hand side of an image's rays shares, once per image:
+    // a lane's ray start then needs no sine, cosine or mass function and no
+    // dispatch on the metric
+    for (int i = threadIdx.x; i < n_images; i += blockDim.x) {
+        const ImageConst& c = lt[i];
+        const Hot h = hot_of(c);
+        lobs[i] = c.metric == CNFW && c.ex_near ? at_observer<CNFW_NEAR>(c, h)
+                  : c.metric == CNFW            ? at_observer<CNFW>(c, h)
+                  : c.metric == EINASTO         ? at_observer<EINASTO>(c, h)
+                                                : at_observer<KERR>(c, h);
+    }
+    __syncthreads();
 
     const fn::Pinned fns = fn::pin<fn::kAll>();
     Ray r;
@@ -115,10 +128,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         px.pix = tile_pixel(ordinal, c.nx, c.ny, shape.tile_w, shape.tile_h, FpQuotient{});
         px.iy = quotient(static_cast<int32_t>(px.pix), c.nx);
         px.ix = static_cast<int32_t>(px.pix) - px.iy * c.nx;
-        if (metric == CNFW_NEAR) start_ray<CNFW_NEAR>(c, k, px, r, fns);
-        else if (metric == CNFW) start_ray<CNFW>(c, k, px, r, fns);
-        else if (metric == EINASTO) start_ray<EINASTO>(c, k, px, r, fns);
-        else start_ray<KERR>(c, k, px, r, fns);
+        start_ray_dir(c, k, lobs[img], screen_dir_ij(c, px.ix, px.iy), px.pix, r);
     };
     for (;;) {
         if (!exhausted) refill(active, exhausted, next, end, claim, take);
@@ -222,7 +232,7 @@ hipError_t launch_emission_batch(const ImageConst* table, const OutPtrs* outs, i
 }
 
 size_t batch_lds_bytes(int32_t n_images) {
-    return sizeof(ImageConst) * static_cast<size_t>(n_images) +
+    return (sizeof(ImageConst) + sizeof(AtObserver)) * static_cast<size_t>(n_images) +
            sizeof(int64_t) * static_cast<size_t>(n_images + 1);
 }
 
