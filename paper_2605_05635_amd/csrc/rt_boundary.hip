@@ -24,7 +24,9 @@
 // holes); without Sigma in the clock it stays at 2e-2.
 //
 // Directions advance independently, each from pass to pass as soon as its own
-// rays end.  4096 directions at S = 16: TIMES; five passes in place of nine.
+// rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 23.0 -> 15.1
+// ms (five to seven passes in place of nine); 1000 at S = 64: 12.6 -> 8.3 ms.
+// What is left is the longest direction's chain, 5924 attempts of 2.4 us.
 #include "rt_ray.h"
 
 namespace rt {
@@ -33,6 +35,11 @@ namespace {
 using namespace ray;
 
 constexpr int kMaxLevels = 64;
+// The prediction lies above the transition by 0.2 W to 0.75 W of the bracket W
+// (the sides' next order); taking off 0.45 W settles 4096 directions at S = 16 in
+// five passes for 3294 of them and in six or seven for the others, against 2823
+// without it (0.25: 3143, 0.7: 3120; the same order in four other spacetimes).
+constexpr double kBias = 0.45;
 
 // What a direction keeps between passes: its two nearest escaping samples with
 // their radial times (b_c < e1 < e2; infinity where there is none), and its two
@@ -169,6 +176,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 // The S - S/4 edges of that level (or of the last before b_tol)
                 // nearest to the prediction, and S/4 of the level above in
                 // case it misses by more.
+                x = fmax(x - kBias * (hi - lo) * (hi - lo), lo);
                 const int coarse = S / 4;
                 const bool fine = sl >= coarse;
                 const int target = fine ? m : m - 1;

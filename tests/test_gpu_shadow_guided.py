@@ -1,0 +1,46 @@
+"""Guided passes of the shadow boundary: their brackets are the bits that uniform
+multisection (the search that counts attempts) ends with, over samples per
+direction, tolerances down to the grid's own resolution, a direction count that
+leaves a partly filled wavefront, and transitions near either end of the bracket."""
+
+import math
+
+import numpy as np
+import pytest
+
+from paper_2605_05635_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # metric, halo, spin, directions, (b_lo, b_hi), b_tol
+    ("kerr", (0.0, 0.0), 0.9, 17, (2.0, 9.0), 1e-10),
+    ("cnfw", (0.02, 10.0), -0.6, 5, (1.0, 30.0), 3e-11),
+    ("einasto", (0.15, 0.0), 0.4, 9, (2.0, 9.0), 1e-12),   # below the finest cell
+    ("kerr", (0.0, 0.0), 0.0, 3, (5.1, 9.0), 1e-9),        # next to b_lo (27^.5 = 5.196)
+    ("kerr", (0.0, 0.0), 0.0, 3, (2.0, 5.25), 1e-9),       # next to b_hi
+    ("kerr", (0.0, 0.0), 0.0, 2, (2.0, 5.0), 1e-9),        # not in the bracket
+    ("cnfw", (0.02, 10.0), 0.94, 4, (2.0, 9.0), 0.5),      # one pass
+]
+
+
+@pytest.mark.parametrize("samples", [16, 32, 64])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}-{c[4]}-{c[5]:g}")
+def test_guided_brackets_are_multisections(case, samples):
+    import torch
+
+    from paper_2605_05635_amd import rt
+    metric, halo, spin, n, (lo, hi), tol = case
+    img = W.image(metric=metric, halo=halo, spin=spin, incl=math.radians(70.0))
+    psi = np.arange(n) * 2.0 * np.pi / n + 0.3
+    d = torch.tensor(np.stack([np.cos(psi), np.sin(psi)], 1), device="cuda")
+    out, st = rt.shadow_boundary(img, d, lo, hi, tol, samples=samples)
+    ref, ref_st = torch.empty_like(out), torch.empty_like(st)
+    attempts = torch.zeros(n, dtype=torch.int64, device="cuda")
+    print(f"[shadow] {case} samples {samples}", flush=True)
+    rt.rt_shadow_boundary(rt.params_from(img), d, lo, hi, tol, ref, ref_st, attempts,
+                          samples=samples)
+    torch.cuda.synchronize()
+    assert torch.equal(st, ref_st)
+    assert torch.equal(out, ref)
+    assert int(attempts.min()) > 0
