@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int grp = lane / S, sl = lane - grp * S;
     const int64_t dir = wave * G + grp;
     const unsigned long long gmask = S == 64 ? ~0ull : ((1ull << S) - 1ull);
-    const fn::Pinned fns = fn::pin<METRIC>();
+    const fn::Pinned fns = fn::pin<METRIC, false, false>();
     const Hot k = hot_of(c);
     const OutPtrs none{};    // no per-pixel outputs
     const bool mine = dir < n;

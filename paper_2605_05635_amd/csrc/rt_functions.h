@@ -32,7 +32,23 @@
 namespace rt {
 namespace fn {
 
+// Dormand-Prince 5(4) tableau (Dormand & Prince 1980, first-same-as-last).
+struct Tableau {
+    double a21 = 0.2;
+    double a31 = 3.0 / 40.0, a32 = 9.0 / 40.0;
+    double a41 = 44.0 / 45.0, a42 = -56.0 / 15.0, a43 = 32.0 / 9.0;
+    double a51 = 19372.0 / 6561.0, a52 = -25360.0 / 2187.0, a53 = 64448.0 / 6561.0, a54 = -212.0 / 729.0;
+    double a61 = 9017.0 / 3168.0, a62 = -355.0 / 33.0, a63 = 46732.0 / 5247.0, a64 = 49.0 / 176.0,
+           a65 = -5103.0 / 18656.0;
+    double b1 = 35.0 / 384.0, b3 = 500.0 / 1113.0, b4 = 125.0 / 192.0, b5 = -2187.0 / 6784.0,
+           b6 = 11.0 / 84.0;
+    // error weights: 5th-order minus embedded 4th-order weights
+    double e1 = 71.0 / 57600.0, e3 = -71.0 / 16695.0, e4 = 71.0 / 1920.0, e5 = -17253.0 / 339200.0,
+           e6 = 22.0 / 525.0, e7 = -1.0 / 40.0;
+};
+
 struct Direct {};
+__host__ __device__ __forceinline__ Tableau tableau(const Direct&) { return Tableau{}; }
 template <class S>
 __host__ __device__ __forceinline__ void sincos(const Direct&, const S& x, S* s_out, S* c_out) {
     dm::sincos(x, s_out, c_out);
@@ -70,7 +86,12 @@ struct PinnedSet {
                      0.0013888888888883752, 0.008333333333326141, 0.04166666666666667,
                      0.1666666666666667};
     double ln2_hi = dm::kLn2Hi, ln2_lo = dm::kLn2Lo, inv_ln2 = dm::kInvLn2;
+    Tableau rk;
 };
+template <bool S>
+__host__ __device__ __forceinline__ const Tableau& tableau(const PinnedSet<S>& q) {
+    return q.rk;
+}
 using Pinned = PinnedSet<false>;
 // The thick disc's kernel has registers for sine's and cosine's coefficients
 // only; those of its exponentials and logarithm go through scalar registers at
@@ -81,7 +102,7 @@ using PinnedThick = PinnedSet<true>;
 // The coefficients as the kernel of a metric holds them: in vector registers,
 // opaque to the compiler so that it cannot turn them back into literals.
 constexpr int kAll = -1;   // every metric's coefficients (the batched kernel)
-template <int METRIC, bool SCALAR = false>
+template <int METRIC, bool SCALAR = false, bool TABLEAU = true>
 __device__ __forceinline__ PinnedSet<SCALAR> pin() {
     PinnedSet<SCALAR> p;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -110,6 +131,21 @@ __device__ __forceinline__ PinnedSet<SCALAR> pin() {
         hold(p.ln2_lo);
         hold(p.inv_ln2);
     }
+    // and as many of the tableau's as every kernel has registers left for without
+    // a spill (image gradients' forward pass is the fullest).  Kerr 64^2 772 -> 744
+    // us, 512^2 1423 -> 1383; Einasto 64^2 883 -> 851; no difference at 1024^2,
+    // where two wavefronts hide the scalar moves, nor for seven in the cored NFW.
+    constexpr int n = SCALAR || !TABLEAU || METRIC == kAll ? 0
+                      : METRIC == KERR                     ? 23
+                      : METRIC == EINASTO                  ? 10
+                      : METRIC == CNFW_NEAR                ? 0
+                                                           : 21;
+    double* const rk[] = {&p.rk.a61, &p.rk.a62, &p.rk.a63, &p.rk.a64, &p.rk.a65, &p.rk.a51, &p.rk.a52,
+                          &p.rk.a53, &p.rk.a54, &p.rk.a41, &p.rk.a42, &p.rk.a43, &p.rk.a31, &p.rk.a32,
+                          &p.rk.b1,  &p.rk.b3,  &p.rk.b4,  &p.rk.b5,  &p.rk.b6,  &p.rk.e1,  &p.rk.e3,
+                          &p.rk.e4,  &p.rk.e5,  &p.rk.e6,  &p.rk.e7,  &p.rk.a21};
+#pragma unroll
+    for (int i = 0; i < n; ++i) hold(*rk[i]);
 #endif
     return p;
 }

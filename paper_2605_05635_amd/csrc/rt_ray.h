@@ -141,20 +141,13 @@ __host__ __device__ __forceinline__ void rhs(const K& k, const S& E, const S& L,
     rhs_c<METRIC>(k, E, L, S(k.chi * E), S(k.chi * L), R, th, pR, pth, d, tb);
 }
 
-// ------------------------------------------------ Dormand-Prince 5(4) tableau
-// Dormand & Prince (1980), first-same-as-last.
-constexpr double a21 = 0.2;
-constexpr double a31 = 3.0 / 40.0, a32 = 9.0 / 40.0;
-constexpr double a41 = 44.0 / 45.0, a42 = -56.0 / 15.0, a43 = 32.0 / 9.0;
-constexpr double a51 = 19372.0 / 6561.0, a52 = -25360.0 / 2187.0, a53 = 64448.0 / 6561.0,
-                 a54 = -212.0 / 729.0;
-constexpr double a61 = 9017.0 / 3168.0, a62 = -355.0 / 33.0, a63 = 46732.0 / 5247.0,
-                 a64 = 49.0 / 176.0, a65 = -5103.0 / 18656.0;
-constexpr double b1 = 35.0 / 384.0, b3 = 500.0 / 1113.0, b4 = 125.0 / 192.0,
-                 b5 = -2187.0 / 6784.0, b6 = 11.0 / 84.0;
-// Error weights: 5th-order minus embedded 4th-order weights.
-constexpr double e1 = 71.0 / 57600.0, e3 = -71.0 / 16695.0, e4 = 71.0 / 1920.0,
-                 e5 = -17253.0 / 339200.0, e6 = 22.0 / 525.0, e7 = -1.0 / 40.0;
+// The tableau by its letters (rt_functions.h).
+constexpr fn::Tableau kRK{};
+constexpr double a21 = kRK.a21, a31 = kRK.a31, a32 = kRK.a32, a41 = kRK.a41, a42 = kRK.a42, a43 = kRK.a43,
+                 a51 = kRK.a51, a52 = kRK.a52, a53 = kRK.a53, a54 = kRK.a54, a61 = kRK.a61,
+                 a62 = kRK.a62, a63 = kRK.a63, a64 = kRK.a64, a65 = kRK.a65;
+constexpr double b1 = kRK.b1, b3 = kRK.b3, b4 = kRK.b4, b5 = kRK.b5, b6 = kRK.b6;
+constexpr double e1 = kRK.e1, e3 = kRK.e3, e4 = kRK.e4, e5 = kRK.e5, e6 = kRK.e6, e7 = kRK.e7;
 // Continuous extension in Hairer's form (Solving ODEs I, II.6):
 //   y(s) = y0 + s (r2 + (1-s)(r3 + s (r4 + (1-s) r5))),
 //   r2 = y1 - y0, r3 = h k1 - r2, r4 = r2 - h k7 - r3, r5 = h sum_i d_i k_i.
@@ -563,6 +556,8 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     if (r.attempts >= k.max_attempts) return RAY_STEP_LIMIT;
     ++r.attempts;
     const double h = r.h;
+    const auto [a21, a31, a32, a41, a42, a43, a51, a52, a53, a54, a61, a62, a63, a64, a65, b1, b3, b4,
+                b5, b6, e1, e3, e4, e5, e6, e7] = fn::tableau(tb);
     double ab[6], ae[6], ad[6];     // sums of b_i k_i, e_i k_i, d_i k_i
     double k2[6], k3[6], k4[6], k5[6], kk[6], t[6];
     sink(0, r.k1);
