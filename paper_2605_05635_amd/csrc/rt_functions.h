@@ -139,7 +139,7 @@ __device__ __forceinline__ PinnedSet<SCALAR> pin() {
                       : METRIC == KERR                     ? 23
                       : METRIC == EINASTO                  ? 10
                       : METRIC == CNFW_NEAR                ? 0
-                                                           : 21;
+                                                           : 19;
     double* const rk[] = {&p.rk.a61, &p.rk.a62, &p.rk.a63, &p.rk.a64, &p.rk.a65, &p.rk.a51, &p.rk.a52,
                           &p.rk.a53, &p.rk.a54, &p.rk.a41, &p.rk.a42, &p.rk.a43, &p.rk.a31, &p.rk.a32,
                           &p.rk.b1,  &p.rk.b3,  &p.rk.b4,  &p.rk.b5,  &p.rk.b6,  &p.rk.e1,  &p.rk.e3,

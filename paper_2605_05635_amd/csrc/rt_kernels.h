@@ -34,12 +34,15 @@ hipError_t launch_zero(unsigned long long* queue, int32_t n, hipStream_t stream)
 // pixels are handed out in chunks of `chunk` consecutive ordinals, ordinals
 // enumerating the screen in tiles of tile_w x tile_h pixels (tile_w = nx,
 // tile_h = 1 is row-major).  With `order` set (n_tiles tile indices, row-major
-// tile numbering), a claim takes one whole tile, tiles in that order.
+// tile numbering), a claim takes one whole tile, tiles in that order, or, in the
+// image trace, a quarter of one once the wavefront's last claim ended past quarter
+// fine_from.
 struct LaunchShape {
     int32_t chunk;
     int32_t tile_w;
     int32_t tile_h;
     const int32_t* order = nullptr;
+    int64_t fine_from = 0;
 };
 
 // Launches the persistent single-image trace kernel of c.metric on `grid`

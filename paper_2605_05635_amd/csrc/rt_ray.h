@@ -836,40 +836,82 @@ __device__ __forceinline__ bool claim_chunk(unsigned long long* queue, int32_t c
 // A wave's current claim in tile-order hand-out (wave-uniform).
 struct TileClaim {
     int32_t x0, y0, w;
-    float inv_w;   // 1/w, for the row of an ordinal inside the tile
+    float inv_w;         // 1/w, for the row of an ordinal inside the tile
+    int64_t part, stop;  // parts claimed and not begun (claim_parts)
 };
 
-// Next claim of a screen's pixels by the whole wave: a chunk of ordinals of
-// the tile enumeration, or the next tile of shape.order (one atomic either
-// way).  Sets the claimed range [next, end) of ordinals within the claim.
-__device__ __forceinline__ bool claim_screen(const LaunchShape& shape, int32_t nx, int32_t ny,
-                                             unsigned long long* queue, int64_t& next,
-                                             int64_t& end, TileClaim& t) {
-    if (!shape.order)
-        return claim_chunk(queue, shape.chunk, static_cast<int64_t>(nx) * ny, next, end);
-    const int32_t tiles_x = (nx + shape.tile_w - 1) / shape.tile_w;
-    const int32_t n_tiles = tiles_x * ((ny + shape.tile_h - 1) / shape.tile_h);
-    unsigned long long q = 0;
-    if (__lane_id() == 0) q = atomicAdd(queue, 1ull);
-    q = __shfl(q, 0);
-    if (static_cast<int64_t>(q) >= n_tiles) return false;
-    const int32_t id = shape.order[q];
+// Tile `id` as the current claim.
+__host__ __device__ __forceinline__ void enter_tile(const LaunchShape& shape, int32_t nx, int32_t tiles_x,
+                                                    int32_t id, TileClaim& t) {
     const int32_t ty = id / tiles_x;
     t.x0 = (id - ty * tiles_x) * shape.tile_w;
     t.y0 = ty * shape.tile_h;
     t.w = nx - t.x0 < shape.tile_w ? nx - t.x0 : shape.tile_w;
     t.inv_w = 1.0f / static_cast<float>(t.w);
-    const int32_t h = ny - t.y0 < shape.tile_h ? ny - t.y0 : shape.tile_h;
-    next = 0;
-    end = static_cast<int64_t>(t.w) * h;
-    return true;
+}
+
+// Claim of tile parts, four to a tile (part j its rows [j h/4, (j + 1) h/4)), in
+// the tiles' order: four parts, or one once the last claim ended past
+// shape.fine_from.  `add(n)` advances the queue by n and returns where it was.
+// Sets the ordinals [next, end) of the claim's parts that lie in one tile; the rest
+// is kept for the next call.  False when the queue is dry.
+template <class Add>
+__host__ __device__ __forceinline__ bool claim_parts(const LaunchShape& shape, int32_t nx, int32_t ny,
+                                                     TileClaim& t, int64_t& next, int64_t& end, Add add) {
+    const int32_t tiles_x = (nx + shape.tile_w - 1) / shape.tile_w;
+    const int64_t n_parts = 4ll * (tiles_x * ((ny + shape.tile_h - 1) / shape.tile_h));
+    for (;;) {
+        if (t.part >= t.stop) {
+            const int n = t.stop < shape.fine_from ? 4 : 1;
+            t.part = add(n);
+            if (t.part >= n_parts) return false;
+            t.stop = t.part + n < n_parts ? t.part + n : n_parts;
+        }
+        const int j = static_cast<int>(t.part & 3), left = static_cast<int>(t.stop - t.part);
+        const int j2 = j + left < 4 ? j + left : 4;
+        enter_tile(shape, nx, tiles_x, shape.order[t.part >> 2], t);
+        t.part += j2 - j;
+        const int32_t h = ny - t.y0 < shape.tile_h ? ny - t.y0 : shape.tile_h;
+        next = static_cast<int64_t>(t.w) * (h / 4 * j + (h % 4 * j >> 2));
+        end = static_cast<int64_t>(t.w) * (h / 4 * j2 + (h % 4 * j2 >> 2));
+        if (next < end) return true;
+    }
+}
+
+// Next claim of a screen's pixels by the whole wave: a chunk of ordinals of
+// the tile enumeration, the next tile of shape.order, or PARTS of it (one atomic
+// each way).  Sets the claimed range [next, end) of ordinals within the claim.
+template <bool PARTS = false>
+__device__ __forceinline__ bool claim_screen(const LaunchShape& shape, int32_t nx, int32_t ny,
+                                             unsigned long long* queue, int64_t& next,
+                                             int64_t& end, TileClaim& t) {
+    if (!shape.order)
+        return claim_chunk(queue, shape.chunk, static_cast<int64_t>(nx) * ny, next, end);
+    auto add = [&](int n) {
+        unsigned long long q = 0;
+        if (__lane_id() == 0) q = atomicAdd(queue, static_cast<unsigned long long>(n));
+        return static_cast<int64_t>(__shfl(q, 0));
+    };
+    if constexpr (PARTS) {
+        return claim_parts(shape, nx, ny, t, next, end, add);
+    } else {
+        const int32_t tiles_x = (nx + shape.tile_w - 1) / shape.tile_w;
+        const int32_t n_tiles = tiles_x * ((ny + shape.tile_h - 1) / shape.tile_h);
+        const int64_t q = add(1);
+        if (q >= n_tiles) return false;
+        enter_tile(shape, nx, tiles_x, shape.order[q], t);
+        const int32_t h = ny - t.y0 < shape.tile_h ? ny - t.y0 : shape.tile_h;
+        next = 0;
+        end = static_cast<int64_t>(t.w) * h;
+        return true;
+    }
 }
 
 // Pixel of ordinal p of the current claim.  Inside a tile the row is
 // floor((p + 1/2)/w) in binary32: exact, since the quotient's fraction stays
 // 1/(2w) away from an integer and its rounding error is ~1e-7 (p/w)
 // (tiles are far smaller than 2^15 pixels), which saves an integer division.
-__device__ __forceinline__ Pixel claimed(const LaunchShape& shape, int32_t nx, int32_t ny,
+__host__ __device__ __forceinline__ Pixel claimed(const LaunchShape& shape, int32_t nx, int32_t ny,
                                          const TileClaim& t, int64_t p) {
     Pixel px;
     if (!shape.order) {

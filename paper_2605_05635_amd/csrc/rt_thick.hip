@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 8))) 
     Ray r;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;
-    TileClaim tc{0, 0, 1, 1.0f};
+    TileClaim tc{0, 0, 1, 1.0f, 0, 0};
     auto claim = [&]() {
         const ImageConst& a = reloaded_args();
         return claim_screen(shape, a.nx, a.ny, queue, next, end, tc);

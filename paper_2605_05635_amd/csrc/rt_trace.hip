@@ -37,8 +37,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     Ray r;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;   // wave-uniform: claimed ordinals not yet started
-    TileClaim tc{0, 0, 1, 1.0f};
-    auto claim = [&]() { return claim_screen(shape, c.nx, c.ny, queue, next, end, tc); };
+    TileClaim tc{0, 0, 1, 1.0f, 0, 0};
+    auto claim = [&]() { return claim_screen<true>(shape, c.nx, c.ny, queue, next, end, tc); };
     auto take = [&](int64_t ordinal) {
         start_ray<METRIC>(c, k, claimed(shape, c.nx, c.ny, tc, ordinal), r, fns);
     };
