@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     bool live = false;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;
-    TileClaim tc{0, 0, 1, 1.0f};
+    TileClaim tc{0, 0, 1, 1.0f, 0, 0};
     uint32_t rays = 0, steps = 0;
     auto claim = [&]() { return claim_screen(shape, c.nx, c.ny, queue, next, end, tc); };
     auto take = [&](int64_t ordinal) {
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void vjp_backward_kernel(
     double xb[4], Eb, Lb, pb[4], rinb;
     bool active = false, exhausted = false;
     int64_t next = 0, end = 0;
-    TileClaim tc{0, 0, 1, 1.0f};
+    TileClaim tc{0, 0, 1, 1.0f, 0, 0};
     // (re)start the recomputation of chunk `chunk` of segment `seg`
     auto begin_chunk = [&]() {
         vjp::load_checkpoint<METRIC>(mine + seg * kVjpCkptDoubles, k, E, L, pix, r);
@@ -304,12 +304,18 @@ __global__ __launch_bounds__(kGradThreads) void grad_partial(const double* __res
     if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-__global__ void grad_final(const double* __restrict__ part, int32_t nblocks,
-                           double* __restrict__ grad) {
+// Four lanes add the partials, each in their order, from LDS: from memory the
+// chain of loads took 34 us.
+__global__ __launch_bounds__(kGradBlocks) void grad_final(const double* __restrict__ part,
+                                                          double* __restrict__ grad) {
+    __shared__ double sh[4 * kGradBlocks];
+    for (int j = 0; j < 4; ++j) sh[j * kGradBlocks + threadIdx.x] = part[j * kGradBlocks + threadIdx.x];
+    __syncthreads();
     const int j = threadIdx.x;
     if (j >= 4) return;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += part[b * 4 + j];
+#pragma unroll 16
+    for (int b = 0; b < kGradBlocks; ++b) s += sh[b * 4 + j];
     grad[j] = s;
 }
 
@@ -385,7 +391,7 @@ hipError_t launch_grad_reduce(const double* grad_pix, int64_t n_pix, double* par
                        n_pix, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_final, dim3(1), dim3(64), 0, stream, partials, kGradBlocks, grad);
+    hipLaunchKernelGGL(grad_final, dim3(1), dim3(kGradBlocks), 0, stream, partials, grad);
     return hipGetLastError();
 }
 
