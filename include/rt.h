@@ -345,9 +345,10 @@ int rt_set_kernel_timing(void *start_event, void *stop_event);
  *   uv         device [K][2] (u, v) pairs
  *   amp        device [K] normalised amplitudes, or NULL
  *   vis        device [K][2] (Re V, Im V), or NULL (not both NULL)
- * Binary64 on the vector ALU, the phases generated in registers (no phase
- * table in memory); fixed summation order, deterministic.  Scratch (16 K ny/16
- * bytes of partial sums and a few KB) is stream-ordered.  RT_ERR_ARG for a bad
+ * Binary64 on the matrix cores, the phases generated in registers (no phase
+ * table in memory); fixed summation order, deterministic.  Scratch (the image's
+ * rows folded about its centre line, 16 bytes per point and partial sum, and a
+ * few KB) is stream-ordered.  RT_ERR_ARG for a bad
  * screen, K < 1 or K > 2^22. */
 int rt_visibility_dft(const double *intensity, const rt_image_params *params, const double *uv,
                       int32_t K, double *amp, double *vis, void *hip_stream);
@@ -457,7 +458,8 @@ int rt_vjp_stats(int64_t *out);
  * applies to later calls on this thread).
  *   order = RT_ORDER_CENTRE (default): a single image's pixels go to
  *     wavefronts in tiles of tile_w x tile_h pixels (0 x 0: 8 x 8), one tile
- *     per claim, tiles ordered by the distance of their centre from the photon
+ *     or, once the launch's lanes are full, a quarter of one per claim, tiles
+ *     ordered by the distance of their centre from the photon
  *     ring's radius around the screen origin (the direction of the hole; the
  *     radius is the critical impact parameter of the metric without spin), so
  *     that the long rays near the ring are traced first and the short ones,

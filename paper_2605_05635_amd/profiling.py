@@ -29,8 +29,8 @@ import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-TRACE_SOURCES = ("rt_trace.hip", "rt_ray.h", "rt_device.h", "rt_math.h", "rt_dual.h",
-                 "rt_kernels.h")
+TRACE_SOURCES = ("rt_trace.hip", "rt_ray.h", "rt_functions.h", "rt_device.h", "rt_math.h",
+                 "rt_dual.h", "rt_kernels.h")
 
 
 def code_tokens(text: str) -> str:
