@@ -996,15 +996,17 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
         (void)hipFreeAsync(mem, stream);
         return code;
     };
-    void* host = nullptr;
-    int rc = staging_reserve(sizeof(rt::VisImage) * n, &host);
-    if (rc != RT_OK) return bail(rc);
-    std::memcpy(host, tab.data(), sizeof(rt::VisImage) * n);
-    if ((e = hipMemcpyAsync(base, host, sizeof(rt::VisImage) * n, hipMemcpyHostToDevice,
-                            stream)) != hipSuccess ||
-        (e = hipEventRecord(g_staging.ready, stream)) != hipSuccess)
-        return bail(hip_fail(e, "visibility table upload"));
-    e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), n,
+    if (n > 1) {
+        void* host = nullptr;
+        const int rc = staging_reserve(sizeof(rt::VisImage) * n, &host);
+        if (rc != RT_OK) return bail(rc);
+        std::memcpy(host, tab.data(), sizeof(rt::VisImage) * n);
+        if ((e = hipMemcpyAsync(base, host, sizeof(rt::VisImage) * n, hipMemcpyHostToDevice,
+                                stream)) != hipSuccess ||
+            (e = hipEventRecord(g_staging.ready, stream)) != hipSuccess)
+            return bail(hip_fail(e, "visibility table upload"));
+    }
+    e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), tab[0], n,
                               static_cast<int32_t>(n_items), max_k,
                               reinterpret_cast<double2*>(base + tab_bytes + flux_bytes),
                               reinterpret_cast<double*>(base + tab_bytes + flux_bytes + part_bytes),

@@ -124,7 +124,8 @@ hipError_t launch_reduce(const ImageConst& c, const double* intensity, double* p
 // the totals.  launch_visibility runs the row fold with the flux partials
 // (fold: n_fold doubles; fpart: kVisFluxBlocks doubles per image), the partial
 // sums (part: n_part double2) and the finish on the device copy d_tab of that
-// table; max_k is the largest K.  Deterministic.
+// table, or for one image on `first` (the table's first, host) and no copy; max_k
+// is the largest K.  Deterministic.
 constexpr int kVisFluxBlocks = 256;   // flux partials per image
 struct VisImage {
     const double* I;
@@ -140,8 +141,9 @@ struct VisImage {
     double x0, dx, y0, dy;
 };
 void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold);
-hipError_t launch_visibility(const VisImage* d_tab, int32_t n_img, int32_t n_items, int32_t max_k,
-                             double2* part, double* fold, double* fpart, hipStream_t stream);
+hipError_t launch_visibility(const VisImage* d_tab, const VisImage& first, int32_t n_img, int32_t n_items,
+                             int32_t max_k, double2* part, double* fold, double* fpart,
+                             hipStream_t stream);
 // Points on n_q rings (radius q[j], device), the first n_dirs of the angles
 // 2 pi a / n_angles: uv [n_q n_dirs][2]; and the average of amp over each
 // ring's n_dirs points (avg) with its amplitude at angle 0 (cut), either

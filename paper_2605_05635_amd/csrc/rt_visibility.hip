@@ -47,17 +47,30 @@ constexpr int kPT = 2, kCT = 4;             // 16-point and 16-column tiles of a
 
 typedef double Acc __attribute__((ext_vector_type(4)));
 
+// Image i of a call: of the device table, or the call's only one, which comes
+// with the kernel's arguments (no table to fill and copy: a single image's call
+// waits for its host, and the copy was a launch of its own).
+template <bool ONE>
+__device__ __forceinline__ const VisImage& image_of(const VisImage* __restrict__ tab, const VisImage& one,
+                                                    int i) {
+    if constexpr (ONE)
+        return one;
+    else
+        return tab[i];
+}
+
 // Folded rows of an image in matrix-operand order: column tile t and row quad
 // q hold 64 values of S then 64 of D, value 16 r + c for row 4 q + r and column
 // 16 t + c (zero beyond the screen), which is the lane order of the right
 // operand.  Block b of image i takes every kVisFluxBlocks-th group of four
 // (tile, quad) cells and leaves the sum of its S values, a partial of the
 // flux, in fpart[i kVisFluxBlocks + b] (fixed order).
+template <bool ONE>
 __global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* __restrict__ tab,
-                                                               double* __restrict__ fold,
+                                                               VisImage one, double* __restrict__ fold,
                                                                double* __restrict__ fpart) {
     __shared__ double sh[kVisThreads];
-    const VisImage& m = tab[blockIdx.y];
+    const VisImage& m = image_of<ONE>(tab, one, static_cast<int>(blockIdx.y));
     const int32_t nx = m.nx, ny = m.ny, nq = m.nq;
     const int32_t h = (ny + 1) / 2;
     const int64_t cells = static_cast<int64_t>(m.nct) * nq;
@@ -94,18 +107,19 @@ __global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* _
 }
 
 // Partial sums of V over one work item.
+template <bool ONE>
 __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void vis_partial_kernel(
-    const VisImage* __restrict__ tab, int32_t n_img, int32_t n_items,
+    const VisImage* __restrict__ tab, VisImage one, int32_t n_img, int32_t n_items,
     const double* __restrict__ fold, double2* __restrict__ part) {
     const int32_t w = __builtin_amdgcn_readfirstlane(
         static_cast<int32_t>(blockIdx.x) * (kVisThreads / 64) + static_cast<int32_t>(threadIdx.x >> 6));
     if (w >= n_items) return;
-    int32_t lo = 0, hi = n_img - 1;   // the image whose items hold w
+    int32_t lo = 0, hi = ONE ? 0 : n_img - 1;   // the image whose items hold w
     while (lo < hi) {
         const int32_t mid = (lo + hi + 1) >> 1;
         if (tab[mid].item0 <= w) lo = mid; else hi = mid - 1;
     }
-    const VisImage& m = tab[lo];
+    const VisImage& m = image_of<ONE>(tab, one, lo);
     // items: point groups fastest, so a block's wavefronts read the same rows
     const int32_t local = w - m.item0;
     const int32_t cell = local / m.nkg, kg = local - cell * m.nkg;
@@ -235,12 +249,13 @@ __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // V_k = dX dY sum over the work items' partials (index order), amp_k = |V_k| / |F|.
+template <bool ONE>
 __global__ __launch_bounds__(kVisThreads) void vis_finish_kernel(const VisImage* __restrict__ tab,
-                                                                 const double2* __restrict__ part,
+                                                                 VisImage one, const double2* __restrict__ part,
                                                                  const double* __restrict__ fpart) {
     __shared__ double sh[kVisThreads];
     static_assert(kVisFluxBlocks == kVisThreads, "one flux partial per thread");
-    const VisImage& m = tab[blockIdx.y];
+    const VisImage& m = image_of<ONE>(tab, one, static_cast<int>(blockIdx.y));
     sh[threadIdx.x] = fpart[blockIdx.y * kVisFluxBlocks + threadIdx.x];
     __syncthreads();
     for (int w = kVisThreads / 2; w > 0; w >>= 1) {
@@ -327,18 +342,28 @@ void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part,
     *n_fold = fold;
 }
 
-hipError_t launch_visibility(const VisImage* d_tab, int32_t n_img, int32_t n_items, int32_t max_k,
-                             double2* part, double* fold, double* fpart, hipStream_t stream) {
-    hipLaunchKernelGGL(vis_fold_kernel, dim3(kVisFluxBlocks, static_cast<unsigned>(n_img)),
-                       dim3(kVisThreads), 0, stream, d_tab, fold, fpart);
+template <bool ONE>
+static void launch_all(const VisImage* tab, const VisImage& one, int32_t n_img, int32_t n_items,
+                       int32_t max_k, double2* part, double* fold, double* fpart, hipStream_t stream) {
+    hipLaunchKernelGGL(vis_fold_kernel<ONE>, dim3(kVisFluxBlocks, static_cast<unsigned>(n_img)),
+                       dim3(kVisThreads), 0, stream, tab, one, fold, fpart);
     const int32_t per_block = kVisThreads / 64;
-    hipLaunchKernelGGL(vis_partial_kernel,
+    hipLaunchKernelGGL(vis_partial_kernel<ONE>,
                        dim3((static_cast<unsigned>(n_items) + per_block - 1) / per_block),
-                       dim3(kVisThreads), 0, stream, d_tab, n_img, n_items, fold, part);
-    hipLaunchKernelGGL(vis_finish_kernel,
+                       dim3(kVisThreads), 0, stream, tab, one, n_img, n_items, fold, part);
+    hipLaunchKernelGGL(vis_finish_kernel<ONE>,
                        dim3(static_cast<unsigned>((max_k + kVisThreads - 1) / kVisThreads),
                             static_cast<unsigned>(n_img)),
-                       dim3(kVisThreads), 0, stream, d_tab, part, fpart);
+                       dim3(kVisThreads), 0, stream, tab, one, part, fpart);
+}
+
+hipError_t launch_visibility(const VisImage* d_tab, const VisImage& first, int32_t n_img, int32_t n_items,
+                             int32_t max_k, double2* part, double* fold, double* fpart,
+                             hipStream_t stream) {
+    if (n_img == 1)
+        launch_all<true>(nullptr, first, 1, n_items, max_k, part, fold, fpart, stream);
+    else
+        launch_all<false>(d_tab, first, n_img, n_items, max_k, part, fold, fpart, stream);
     return hipGetLastError();
 }
 
