@@ -35,6 +35,7 @@ namespace {
 using namespace ray;
 
 constexpr int kMaxLevels = 64;
+constexpr int kMay = 1, kDid = 2;   // a direction may run guided passes, has run one
 // The prediction lies above the transition by 0.2 W to 0.75 W of the bracket W
 // (the sides' next order); taking off 0.45 W settles 4096 directions at S = 16 in
 // five passes for 3294 of them and in six or seven for the others, against 2823
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     bool done = !mine;
     // A caller that counts attempts gets the count of uniform passes.
     bool guided = false;     // the next pass (group-uniform)
-    const bool may_guide = attempts == nullptr;
+    int guide = attempts == nullptr ? kMay : 0;
     // Pass -1 checks the bracket (sample 0 at b_lo must stay inside, sample 1
     // at b_hi must escape); the passes after it search.  Each group runs its
     // passes on its own: when the last of its rays ends it narrows its bracket
@@ -173,6 +174,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 cells *= S + 1;
             }
             if (guided && m > 1 && w > finest && predict(near, &x)) {
+                guide |= kDid;
                 // The S - S/4 edges of that level (or of the last before b_tol)
                 // nearest to the prediction, and S/4 of the level above in
                 // case it misses by more.
@@ -206,6 +208,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         if (active)
             start_ray_dir<METRIC>(c, k, screen_dir_xy(c, b * dirs[2 * dir], b * dirs[2 * dir + 1]), 0, r, fns);
     };
+    // A ray that ran out of attempts, or whose error estimate was not finite,
+    // counts as inside on either side of the transition, so the samples a
+    // guided pass left out could have mattered: the direction goes on by
+    // uniform passes, from the start if it had a guided one (true).
+    auto redo = [&]() {
+        int odd = fate != 0 && fate != RAY_ESCAPED && fate != RAY_CAPTURED;
+        for (int off = 1; off < S; off <<= 1) odd |= __shfl_xor(odd, off);
+        if (odd) guide &= ~kMay;
+        if (guide != kDid) return false;
+        guide = 0;
+        near.e1 = near.e2 = INFINITY;
+        near.c1 = near.c2 = -INFINITY;
+        near.lo = b_lo;
+        near.hi = b_hi;
+        return true;
+    };
     if (!done) start_pass();
     while (__ballot(!done) != 0ull) {
         if (active) {
@@ -231,6 +249,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 }
                 level = 0;
                 if (!(b_hi - b_lo > b_tol)) done = true;
+            } else if (redo()) {
+                level = 0;
+                guided = false;
             } else {
                 // nearest samples on either side of the transition, the first
                 // escaping sample
@@ -283,7 +304,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 near.lo = lo;
                 near.hi = hi;
                 // (a guided pass that settled nothing is followed by a uniform one)
-                guided = may_guide && level >= 2 && level > before;
+                guided = (guide & kMay) && level >= 2 && level > before;
             }
             if (!done) start_pass();
         }

@@ -44,3 +44,29 @@ def test_guided_brackets_are_multisections(case, samples):
     assert torch.equal(st, ref_st)
     assert torch.equal(out, ref)
     assert int(attempts.min()) > 0
+
+
+@pytest.mark.parametrize("metric,halo,spin,incl,samples,max_attempts", [
+    ("cnfw", (0.026591071355334964, 8.124849903947785), 0.3562084272295464, 0.4731523157197913, 32, 649),
+    ("kerr", (0.0, 0.0), 0.13626928861037746, 2.903320946624731, 64, 416),
+    ("cnfw", (0.16527745632976956, 10.842416819431184), -0.6794538286157996, 2.9009015502112625, 64, 492),
+    ("einasto", (0.15, 0.0), 0.4, 1.2, 16, 250),
+])
+def test_rays_out_of_attempts(metric, halo, spin, incl, samples, max_attempts):
+    """Rays that end by the attempt limit count as inside wherever they are, so which
+    edges are sampled could decide; such directions go by uniform passes."""
+    import torch
+
+    from paper_2605_05635_amd import rt
+    n = 200
+    img = W.image(metric=metric, halo=halo, spin=spin, incl=incl, max_attempts=max_attempts)
+    psi = (np.arange(n) + 0.3) * 2 * np.pi / n
+    d = torch.tensor(np.stack([np.cos(psi), np.sin(psi)], 1), device="cuda")
+    print(f"[shadow] {metric} samples {samples} max_attempts {max_attempts}", flush=True)
+    out, st = rt.shadow_boundary(img, d, 2.0, 9.0, 1e-10, samples=samples)
+    ref, ref_st = torch.empty_like(out), torch.empty_like(st)
+    attempts = torch.zeros(n, dtype=torch.int64, device="cuda")
+    rt.rt_shadow_boundary(rt.params_from(img), d, 2.0, 9.0, 1e-10, ref, ref_st, attempts, samples=samples)
+    torch.cuda.synchronize()
+    assert torch.equal(st, ref_st)
+    assert torch.equal(out, ref)
