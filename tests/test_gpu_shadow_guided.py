@@ -70,3 +70,24 @@ def test_rays_out_of_attempts(metric, halo, spin, incl, samples, max_attempts):
     torch.cuda.synchronize()
     assert torch.equal(st, ref_st)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("tol,b_tol", [(1e-2, 1e-8), (1e-4, 1e-10), (2e-6, 1e-9), (1e-6, 1e-10), (1e-7, 1e-10)])
+def test_loose_integrations(tol, b_tol):
+    """Fates are out of order within the integration's error of the transition: loose
+    ones are searched by uniform passes, and from 1e-6 down guided passes agree."""
+    import torch
+
+    from paper_2605_05635_amd import rt
+    n = 300
+    img = W.image(metric="cnfw", halo=(0.05, 8.0), spin=0.7, incl=1.1, rtol=tol, atol=tol)
+    psi = (np.arange(n) + 0.3) * 2 * np.pi / n
+    d = torch.tensor(np.stack([np.cos(psi), np.sin(psi)], 1), device="cuda")
+    print(f"[shadow] tolerance {tol}", flush=True)
+    out, st = rt.shadow_boundary(img, d, 2.0, 9.0, b_tol, samples=16)
+    ref, ref_st = torch.empty_like(out), torch.empty_like(st)
+    attempts = torch.zeros(n, dtype=torch.int64, device="cuda")
+    rt.rt_shadow_boundary(rt.params_from(img), d, 2.0, 9.0, b_tol, ref, ref_st, attempts, samples=16)
+    torch.cuda.synchronize()
+    assert torch.equal(st, ref_st)
+    assert torch.equal(out, ref)
