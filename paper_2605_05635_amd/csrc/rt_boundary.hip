@@ -39,10 +39,11 @@ constexpr int kMaxLevels = 64;
 // Looser integrations search by uniform passes.  Fates are out of order within the
 // integration's error of the transition, where an accept or reject decision flips
 // between neighbouring rays, and samples that a guided pass leaves out can
-// then miss a flip: of 200 directions each in 240 random spacetimes, tolerances
-// and brackets, its bracket was another one for 0 of 28,600 below 1e-5, 71 of 19,400 from
-// 1e-5 to 1e-2 (2874 of 48,000 from 1e-6 without the test of order below).
-constexpr double kGuidedTol = 1e-6;
+// then miss a flip: with guided passes at every tolerance the bracket was another
+// one for none of 184,320 directions at 1e-8 (S = 16) and of 98,304 at 1e-7, for 17 of
+// 86,016 at 1e-6 and for 71 of 19,400 from 1e-5 to 1e-2 (one in 17 from 1e-6 to
+// 1e-2 without the test of order in redo below).
+constexpr double kGuidedTol = 1e-7;
 constexpr int kMay = 1, kDid = 2;   // a direction may run guided passes, has run one
 // The prediction lies above the transition by 0.2 W to 0.75 W of the bracket W
 // (the sides' next order); taking off 0.45 W settles 4096 directions at S = 16 in

@@ -75,7 +75,7 @@ def test_rays_out_of_attempts(metric, halo, spin, incl, samples, max_attempts):
 @pytest.mark.parametrize("tol,b_tol", [(1e-2, 1e-8), (1e-4, 1e-10), (2e-6, 1e-9), (1e-6, 1e-10), (1e-7, 1e-10)])
 def test_loose_integrations(tol, b_tol):
     """Fates are out of order within the integration's error of the transition: loose
-    ones are searched by uniform passes, and from 1e-6 down guided passes agree."""
+    ones are searched by uniform passes, and from 1e-7 down guided passes agree."""
     import torch
 
     from paper_2605_05635_amd import rt
