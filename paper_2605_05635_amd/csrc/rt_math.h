@@ -293,16 +293,9 @@ __host__ __device__ inline LogSplit log_split(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
     uint32_t hi = static_cast<uint32_t>(b >> 32) + (0x3ff00000u - 0x3fe6a09eu);
     LogSplit s;
-#if defined(__HIP_DEVICE_COMPILE__)
-    // m = v 2^-e by one exponent instruction in place of the mask and the add
-    const int32_t ne = 0x3ff - static_cast<int32_t>(hi >> 20);
-    s.e = -static_cast<double>(ne);
-    s.m = __builtin_amdgcn_ldexp(v, ne);
-#else
     s.e = static_cast<double>(static_cast<int32_t>(hi >> 20) - 0x3ff);
     hi = (hi & 0x000fffffu) + 0x3fe6a09eu;
     s.m = __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | (b & 0xffffffffull));
-#endif
     return s;
 }
 
