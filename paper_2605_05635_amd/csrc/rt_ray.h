@@ -96,7 +96,6 @@ __host__ __device__ __forceinline__ void rhs_at(const K& k, const S& E, const S&
     const S R2c = R2 + k.chi2;
     const S Sig = R2 + k.chi2 * co * co;
     const S Del = R2c - F;
-    const S hDel = R - half * dF;   // half of dDelta/dR
     // 1/Sigma, 1/Delta and 1/sin(theta) from one reciprocal of their product
     const S SD = Sig * Del;
     const S inv = rcp(SD * s);
@@ -109,7 +108,13 @@ __host__ __device__ __forceinline__ void rhs_at(const K& k, const S& E, const S&
     const S Lis2 = L * is * is;
     const S W = L * is - chiE * s;
     const S N = Del * pR * pR + pth * pth - P * PiD + W * W;
-    const S hdN = hDel * (pR * pR + PiD * PiD) - two * R * E * PiD;   // half of dN/dR
+    // half of dN/dR: the halves are exact, which saves an operation, except
+    // where binary32 over- or underflows
+    S hdN;
+    if constexpr (std::is_same<S, float>::value)
+        hdN = half * ((two * R - dF) * (pR * pR + PiD * PiD) - S(4.0) * R * E * PiD);
+    else
+        hdN = (R - half * dF) * (pR * pR + PiD * PiD) - two * R * E * PiD;
     d[0] = (PiD * R2c + k.chi * (L - chiE * s * s)) * iS;
     d[1] = Del * pR * iS;
     d[2] = pth * iS;
