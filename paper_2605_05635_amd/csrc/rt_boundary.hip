@@ -217,28 +217,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         if (active)
             start_ray_dir<METRIC>(c, k, screen_dir_xy(c, b * dirs[2 * dir], b * dirs[2 * dir + 1]), 0, r, fns);
     };
-    // Whether the direction has to begin again without guided passes.  The edges
-    // they leave out do not matter as long as fates are in order, captured
-    // below the transition and escaping above.  A ray that ran out of attempts or
-    // whose error estimate was not finite counts as inside on either side,
-    // and a sample that ended inside above one that escaped is out of
-    // order: from either on, the direction goes by uniform passes.  (Below
-    // `finest` the passes are uniform in any case.)
+    // Whether this pass's samples are dropped.  The edges that guided passes leave
+    // out do not matter as long as fates are in order, captured below the
+    // transition and escaping above.  A sample that ended inside above one that
+    // escaped is out of order: the direction goes on by uniform passes from the
+    // bracket that it had.  (Below `finest` they are uniform in any case.)  A ray
+    // that ran out of attempts or whose error estimate was not finite counts as
+    // inside on either side: from the start by uniform passes.
     auto redo = [&]() {
         double out_b = traced && fate == RAY_ESCAPED ? b : INFINITY, t = 0.0;
         group_min(out_b, t, S);
         out_b = fmin(out_b, near.e1);
-        int odd = (fate != 0 && fate != RAY_ESCAPED && fate != RAY_CAPTURED) ||
-                  (near.hi - near.lo > finest && (near.c1 > out_b || (traced && fate != RAY_ESCAPED && b > out_b)));
+        const bool lost = fate != 0 && fate != RAY_ESCAPED && fate != RAY_CAPTURED;
+        const bool order = near.hi - near.lo > finest &&
+                           (near.c1 > out_b || (traced && fate != RAY_ESCAPED && b > out_b));
+        int odd = lost ? 2 : order ? 1 : 0;
         for (int off = 1; off < S; off <<= 1) odd |= __shfl_xor(odd, off);
-        if (odd) guide &= ~kMay;
-        if (guide != kDid) return false;
+        if (odd == 0 || !(guide & kMay)) return false;
+        const bool drop = guide & kDid;
         guide = 0;
-        near.e1 = near.e2 = INFINITY;
-        near.c1 = near.c2 = -INFINITY;
-        near.lo = b_lo;
-        near.hi = b_hi;
-        return true;
+        if (drop && (odd & 2)) {
+            near.e1 = near.e2 = INFINITY;
+            near.c1 = near.c2 = -INFINITY;
+            near.lo = b_lo;
+            near.hi = b_hi;
+            level = 0;
+        }
+        return drop;
     };
     if (!done) start_pass();
     while (__ballot(!done) != 0ull) {
@@ -266,7 +271,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 level = 0;
                 if (!(b_hi - b_lo > b_tol)) done = true;
             } else if (redo()) {
-                level = 0;
                 guided = false;
             } else {
                 // nearest samples on either side of the transition, the first
