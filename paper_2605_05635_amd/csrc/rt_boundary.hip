@@ -27,7 +27,8 @@
 // Directions advance independently, each from pass to pass as soon as its own
 // rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 23.0 -> 15.1
 // ms (five to seven passes in place of nine); 1000 at S = 64: 12.6 -> 8.3 ms.
-// What is left is the longest direction's chain, 5924 attempts of 2.4 us.
+// What is left is the longest direction's chain, 5924 attempts of 2.4 us; 20
+// ms in one call of ten, where some direction came out of order (redo).
 #include "rt_ray.h"
 
 namespace rt {
