@@ -94,10 +94,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     search::Sample p{0.0, 0.0, false, 0};   // this lane's sample
     bool active = false;                    // its ray is in flight
     auto start_pass = [&]() {
-        p = search::choose(q, sl, near, course);
+        const double ux = dirs[2 * dir], uy = dirs[2 * dir + 1];
+        p = search::choose(q, sqrt(ux * ux + uy * uy), sl, near, course);
         active = p.traced;
-        if (active)
-            start_ray_dir<METRIC>(c, k, screen_dir_xy(c, p.b * dirs[2 * dir], p.b * dirs[2 * dir + 1]), 0, r, fns);
+        if (active) start_ray_dir<METRIC>(c, k, screen_dir_xy(c, p.b * ux, p.b * uy), 0, r, fns);
     };
     if (!course.done) start_pass();
     while (__ballot(!course.done) != 0ull) {

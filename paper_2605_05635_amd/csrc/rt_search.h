@@ -15,7 +15,7 @@
 // / Sigma (which the polar motion does not enter) diverges as -a ln|b - b_c|
 // with the same a on both sides.  Two escaping and two captured samples next to
 // the transition give a and b_c.  The error left, in units of the bracket W
-// that held the samples, is of second order, about W/2 until W ~ 1e-3, and
+// that held the samples, is of second order, about W/2 until W ~ 1e-3 M, and
 // below 1e-4 from there (measured over 12 directions of the cored-NFW and Kerr
 // holes); without Sigma in the clock it stays at 2e-2.
 #pragma once
@@ -134,10 +134,12 @@ __host__ __device__ __forceinline__ void begin(const Search& q, bool may, N& n, 
     s.done = false;
 }
 
-// Lane sl's sample of the next pass.  Level -1 checks the bracket: sample 0 at
+// Lane sl's sample of the next pass along a direction of this length (b times it is
+// the impact parameter in M).  Level -1 checks the bracket: sample 0 at
 // b_lo must stay inside, sample 1 at b_hi must escape.
 template <class N>
-__host__ __device__ __forceinline__ Sample choose(const Search& q, int sl, const N& n, Course& s) {
+__host__ __device__ __forceinline__ Sample choose(const Search& q, double length, int sl, const N& n,
+                                                   Course& s) {
     const int S = q.S;
     const double lo = n.lo, hi = n.hi;
     const double w = (hi - lo) / (S + 1);
@@ -149,7 +151,8 @@ __host__ __device__ __forceinline__ Sample choose(const Search& q, int sl, const
     }
     // The finest level, at most three down, whose cells the prediction
     // is expected to miss by no more than S / 4.
-    const double miss = 0.5 * (hi - lo) + 3e-4;   // in units of the bracket
+    const double W = (hi - lo) * length;
+    const double miss = 0.5 * W + 3e-4;   // in units of the bracket
     int m = 1;
     double cells = miss * (S + 1);
     while (m < 3 && cells * (S + 1) <= 0.25 * S) {
@@ -162,7 +165,7 @@ __host__ __device__ __forceinline__ Sample choose(const Search& q, int sl, const
         // The S - S/4 edges of that level (or of the last before b_tol)
         // nearest to the prediction, and S/4 of the level above in
         // case it misses by more.
-        x = fmax(x - kBias * (hi - lo) * (hi - lo), lo);
+        x = fmax(x - kBias * W * (hi - lo), lo);
         const int coarse = S / 4;
         const bool fine = sl >= coarse;
         const int target = fine ? m : m - 1;

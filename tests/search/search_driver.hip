@@ -1,9 +1,9 @@
 // Host driver for tests/test_search.py: the shadow boundary's decisions
 // (paper_2605_05635_amd/csrc/rt_search.h, compiled for the host from the same source) on scripted rays.
-//   row = S b_lo b_hi b_tol b_c jump period lost seed
+//   row = S b_lo b_hi b_tol b_c jump period lost seed length
 // A ray at b escapes above b_c + shift(b), a step function of b as an accept or reject decision that flips
 // between neighbouring rays makes it: on each interval of length `period` another value within +-jump.  Within
-// `lost` of b_c it runs out of attempts with probability 1/4.
+// `lost` of b_c it runs out of attempts with probability 1/4.  `length` is the direction's.
 //   out: lo, hi, passes, the samples traced, whether a pass was dropped
 #include <cmath>
 #include <cstdint>
@@ -61,9 +61,9 @@ void ray(const double* a, search::Sample& p) {
 }  // namespace
 
 int main() {
-    double a[9];
+    double a[10];
     std::vector<double> out;
-    while (std::fread(a, sizeof(double), 9, stdin) == 9) {
+    while (std::fread(a, sizeof(double), 10, stdin) == 10) {
         const search::Search q{static_cast<int>(a[0]), a[1], a[2], a[3]};
         search::Nearest near;
         search::Course course;
@@ -73,7 +73,7 @@ int main() {
         course.level = 0;
         while (!course.done) {
             for (int sl = 0; sl < q.S; ++sl) {
-                lanes[sl] = search::choose(q, sl, near, course);
+                lanes[sl] = search::choose(q, a[9], sl, near, course);
                 if (lanes[sl].traced) {
                     ray(a, lanes[sl]);
                     traced += 1.0;

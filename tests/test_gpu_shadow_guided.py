@@ -91,3 +91,23 @@ def test_loose_integrations(tol, b_tol):
     torch.cuda.synchronize()
     assert torch.equal(st, ref_st)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("length", [2.0 ** -7, 1.0, 2.0 ** 10])
+def test_direction_lengths(length):
+    """b is in units of the direction's length; guided passes go by the impact parameter."""
+    import torch
+
+    from paper_2605_05635_amd import rt
+    n = 100
+    img = W.image(metric="cnfw", halo=(0.02, 10.0), spin=0.94, incl=1.2)
+    psi = (np.arange(n) + 0.3) * 2 * np.pi / n
+    d = torch.tensor(np.stack([np.cos(psi), np.sin(psi)], 1), device="cuda")
+    print(f"[shadow] directions of length {length}", flush=True)
+    ref, ref_st = torch.empty(n, 2, dtype=torch.float64, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    attempts = torch.zeros(n, dtype=torch.int64, device="cuda")
+    rt.rt_shadow_boundary(rt.params_from(img), d, 2.0, 9.0, 1e-10, ref, ref_st, attempts, samples=16)
+    out, st = rt.shadow_boundary(img, d * length, 2.0 / length, 9.0 / length, 1e-10 / length, samples=16)
+    torch.cuda.synchronize()
+    assert torch.equal(st, ref_st)
+    assert torch.equal(out * length, ref)

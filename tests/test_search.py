@@ -35,7 +35,7 @@ def hashed(x, seed):
 
 
 def escapes(row, b):
-    b_c, jump, period, lost, seed = row[4:]
+    b_c, jump, period, lost, seed = row[4:9]
     d, seed = b - b_c, int(seed)
     out = d > jump * (2.0 * hashed(float(np.floor(d / period)), seed) - 1.0)
     return out and not (abs(d) < lost and hashed(b, seed + 1) < 0.25)
@@ -59,7 +59,7 @@ def multisection(row):
 def rows(S, n, b_tol, jump=0.0, period=1.0, lost=0.0):
     r = np.random.default_rng(S)
     return np.stack([np.full(n, float(S)), np.full(n, 2.0), np.full(n, 9.0), np.full(n, b_tol), r.uniform(2.5, 8.5, n),
-                     np.full(n, jump), np.full(n, period), np.full(n, lost), np.arange(n) * 2.0], axis=1)
+                     np.full(n, jump), np.full(n, period), np.full(n, lost), np.arange(n) * 2.0, np.ones(n)], axis=1)
 
 
 @pytest.mark.parametrize("S", [16, 32, 64])
@@ -90,3 +90,16 @@ def test_out_of_order(driver, S, jump, period, lost):
     assert seen.sum() > 20
     assert not any(escapes(x, y) for x, y in zip(a, d[:, 0])) and all(escapes(x, y) for x, y in zip(a, d[:, 1]))
     assert [tuple(x) for x in d[seen, :2]] == [multisection(x) for x in a[seen]]
+
+
+@pytest.mark.parametrize("S", [16, 64])
+@pytest.mark.parametrize("length", [2.0 ** -7, 2.0 ** 10])
+def test_direction_length(driver, S, length):
+    """b is in units of the direction's length: the same rays in the same passes."""
+    a = rows(S, 300, 1e-10)
+    scaled = a.copy()
+    scaled[:, 1:5] /= length
+    scaled[:, 9] = length
+    d, e = driver(a), driver(scaled)
+    assert np.array_equal(d[:, :2], e[:, :2] * length)
+    assert np.array_equal(d[:, 2:], e[:, 2:])
