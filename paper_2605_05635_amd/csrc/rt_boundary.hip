@@ -11,8 +11,9 @@
 // ones settle two or three levels at once.
 //
 // Directions advance independently, each from pass to pass as soon as its own
-// rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 23.0 -> 15.1
-// ms (five to seven passes in place of nine); 1000 at S = 64: 12.6 -> 8.3 ms.
+// rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 21.7 ms by uniform
+// passes, 14.7 by guided ones (five to seven passes in place of nine); 500 at S = 64:
+// 14.0 and 9.7 ms.
 // What is left is the longest direction's chain, 5924 attempts of 2.4 us; 21 ms in
 // one call of ten, where some direction came out of order, and over 40 in one of
 // thirty, where it started again from its uniform bracket (search::redo).
@@ -62,13 +63,17 @@ struct GroupLanes {
     }
 };
 
-// Register-allocated like the trace kernel.
-template <int METRIC>
+// GUIDED passes where they may run, else uniform ones, which need neither the
+// radial time nor the nearest samples (with both kinds in one kernel, uniform
+// searches took 3 to 6 % longer: Kerr at a tolerance of 1e-5 5.64 -> 5.37 ms).  Registers as the trace kernel's, the
+// tableau not pinned; the guided kernels of Einasto and of the near cored NFW
+// spill 22 and 26 of them, in the code between passes.
+template <int METRIC, bool GUIDED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void boundary_kernel(
     ImageConst c, const double* __restrict__ dirs, int32_t n, int32_t S, double b_lo, double b_hi,
     double b_tol, double* __restrict__ out, int32_t* __restrict__ status,
     int64_t* __restrict__ attempts) {
-    __shared__ search::Nearest kept[kBlock / 16];   // one per direction, written alike by all its lanes
+    __shared__ search::Nearest kept[GUIDED ? kBlock / 16 : 1];   // one per direction, written alike by all its lanes
     const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) / 64;
     const int lane = __lane_id();
     const int G = 64 / S;                    // directions per wavefront
@@ -80,10 +85,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const OutPtrs none{};    // no per-pixel outputs
     const bool mine = dir < n;
     const search::Search q{S, b_lo, b_hi, b_tol};
-    volatile search::Nearest& near = kept[(threadIdx.x / 64) * 4 + grp];
-    search::Course course;
-    // (a caller that counts attempts gets the count of uniform passes)
-    search::begin(q, attempts == nullptr && fmax(c.rtol, c.atol) <= kGuidedTol, near, course);
+    volatile search::Nearest& near = kept[GUIDED ? (threadIdx.x / 64) * 4 + grp : 0];
+    search::Course course{};
+    double lo = b_lo, hi = b_hi;   // the bracket of uniform passes
+    course.level = -1;
+    if constexpr (GUIDED) search::begin(q, near, course);
     course.done = !mine;
     int64_t used = 0;        // this lane's step attempts
     int32_t result = 1;      // bracket without the transition, until checked
@@ -95,7 +101,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     bool active = false;                    // its ray is in flight
     auto start_pass = [&]() {
         const double ux = dirs[2 * dir], uy = dirs[2 * dir + 1];
-        p = search::choose(q, sqrt(ux * ux + uy * uy), sl, near, course);
+        if constexpr (GUIDED) {
+            p = search::choose(q, sqrt(ux * ux + uy * uy), sl, near, course);
+        } else {
+            p.b = course.level < 0 ? (sl == 0 ? b_lo : b_hi) : search::edge(lo, hi, (hi - lo) / (S + 1), sl + 1, S);
+            p.traced = course.level >= 0 || sl < 2;
+            p.fate = 0;
+        }
         active = p.traced;
         if (active) start_ray_dir<METRIC>(c, k, screen_dir_xy(c, p.b * ux, p.b * uy), 0, r, fns);
     };
@@ -108,7 +120,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 p.fate = st;
                 // the radial time at the stop radius itself
                 const double stop = st == RAY_ESCAPED ? k.r_esc : k.r_stop;
-                p.tau = r.tau + (stop - r.y[1]) * (r.iS / r.k1[1]);
+                if constexpr (GUIDED) p.tau = r.tau + (stop - r.y[1]) * (r.iS / r.k1[1]);
                 used += r.attempts;
             }
         }
@@ -124,8 +136,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
                 }
                 course.level = 0;
                 if (!(b_hi - b_lo > b_tol)) course.done = true;
-            } else {
+            } else if constexpr (GUIDED) {
                 search::narrow(q, GroupLanes{p, S}, near, course);
+            } else {
+                course.done = search::narrow_uniform(q, esc != 0ull ? __ffsll(static_cast<long long>(esc)) : S + 1,
+                                                     lo, hi, course.level);
             }
             if (!course.done) start_pass();
         }
@@ -133,8 +148,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // the group's attempt total, in a fixed order
     for (int off = S / 2; off > 0; off >>= 1) used += __shfl_xor(used, off);
     if (mine && sl == 0) {
-        out[2 * dir] = near.lo;
-        out[2 * dir + 1] = near.hi;
+        out[2 * dir] = GUIDED ? near.lo : lo;
+        out[2 * dir + 1] = GUIDED ? near.hi : hi;
         status[dir] = result;
         if (attempts) attempts[dir] = used;
     }
@@ -147,18 +162,20 @@ hipError_t launch_boundary(const ImageConst& c, const double* dirs, int32_t n, i
                            int64_t* attempts, hipStream_t stream) {
     const int64_t waves = (static_cast<int64_t>(n) * samples + 63) / 64;
     const int32_t blocks = static_cast<int32_t>((waves + kBlock / 64 - 1) / (kBlock / 64));
+    // (a caller that counts attempts gets the count of uniform passes)
+    const bool guided = attempts == nullptr && std::fmax(c.rtol, c.atol) <= kGuidedTol;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, stream, c, dirs, n, samples, b_lo, b_hi,
+                           b_tol, out, status, attempts);
+    };
     if (c.metric == KERR)
-        hipLaunchKernelGGL(boundary_kernel<KERR>, dim3(blocks), dim3(kBlock), 0, stream, c, dirs,
-                           n, samples, b_lo, b_hi, b_tol, out, status, attempts);
+        guided ? launch(boundary_kernel<KERR, true>) : launch(boundary_kernel<KERR, false>);
     else if (c.metric == EINASTO)
-        hipLaunchKernelGGL(boundary_kernel<EINASTO>, dim3(blocks), dim3(kBlock), 0, stream, c,
-                           dirs, n, samples, b_lo, b_hi, b_tol, out, status, attempts);
+        guided ? launch(boundary_kernel<EINASTO, true>) : launch(boundary_kernel<EINASTO, false>);
     else if (c.ex_near)
-        hipLaunchKernelGGL(boundary_kernel<CNFW_NEAR>, dim3(blocks), dim3(kBlock), 0, stream, c,
-                           dirs, n, samples, b_lo, b_hi, b_tol, out, status, attempts);
+        guided ? launch(boundary_kernel<CNFW_NEAR, true>) : launch(boundary_kernel<CNFW_NEAR, false>);
     else
-        hipLaunchKernelGGL(boundary_kernel<CNFW>, dim3(blocks), dim3(kBlock), 0, stream, c, dirs,
-                           n, samples, b_lo, b_hi, b_tol, out, status, attempts);
+        guided ? launch(boundary_kernel<CNFW, true>) : launch(boundary_kernel<CNFW, false>);
     return hipGetLastError();
 }
 

@@ -120,8 +120,16 @@ __host__ __device__ __forceinline__ bool predict(const N& n, double* x_out) {
     return true;
 }
 
+// The bracket after a uniform pass, from its first escaping edge (S + 1: none).
+// Returns whether the search has ended.
+__host__ __device__ __forceinline__ bool narrow_uniform(const Search& q, int first, double& lo, double& hi, int& level) {
+    const double was_lo = lo, was_hi = hi;
+    cell(lo, hi, (hi - lo) / (q.S + 1), first, q.S);
+    return ++level >= kMaxLevels || (lo == was_lo && hi == was_hi) || !(hi - lo > q.b_tol);
+}
+
 template <class N>
-__host__ __device__ __forceinline__ void begin(const Search& q, bool may, N& n, Course& s) {
+__host__ __device__ __forceinline__ void begin(const Search& q, N& n, Course& s) {
     n.e1 = n.e2 = INFINITY;
     n.c1 = n.c2 = -INFINITY;
     n.te1 = n.te2 = n.tc1 = n.tc2 = 0.0;
@@ -129,7 +137,7 @@ __host__ __device__ __forceinline__ void begin(const Search& q, bool may, N& n, 
     n.hi = n.uhi = q.b_hi;
     n.ulevel = 0;
     s.level = -1;
-    s.guide = may ? kMay : 0;
+    s.guide = kMay;
     s.guided = false;
     s.done = false;
 }

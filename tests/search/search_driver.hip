@@ -67,7 +67,7 @@ int main() {
         const search::Search q{static_cast<int>(a[0]), a[1], a[2], a[3]};
         search::Nearest near;
         search::Course course;
-        search::begin(q, true, near, course);
+        search::begin(q, near, course);
         std::vector<search::Sample> lanes(static_cast<size_t>(q.S));
         double passes = 0.0, traced = 0.0, dropped = 0.0;
         course.level = 0;
