@@ -24,7 +24,7 @@
 //   * the item's 64 columns are then summed with exp(-2 pi i (u X + v Y_c)).
 // Each work item writes one partial sum per point; a last kernel adds a
 // point's partials in index order, scales by dX dY and divides by the flux.
-// Deterministic run to run, and the split of an image depends on it alone.
+// Deterministic run to run, and the split of an image depends on its size alone.
 //
 // Bound by the binary64 matrix rate: a probe of independent
 // v_mfma_f64_16x16x4 reaches 77 TFLOP/s on this card (71 with one wavefront
@@ -312,13 +312,12 @@ __global__ void ring_average_kernel(const double* __restrict__ amp, int32_t n_q,
 
 }  // namespace
 
-// The split of an image into work items: 32 points x 64 columns, and as many
-// row segments (of 32 quads = 256 image rows or more) as bring it to about
-// kVisWaves wavefronts, four per SIMD: an image of 1024^2 at 1024 points has
-// 512 pairs of point and column blocks, which alone would leave half of the
-// SIMDs without a wavefront.
-constexpr int64_t kVisWaves = 4096;
-
+// The split of an image into work items: 32 points x 64 columns x a segment of its
+// rows.  An image of 1024^2 at 1024 points has 512 pairs of point and column
+// blocks, which alone would leave half of the SIMDs without a wavefront: a
+// segment for every 32 quads (256 image rows) or part of it.  The split is the
+// image's, whatever the number of points, and with it a point's bits (1024^2, 60,000
+// points: 2.47 ms with one segment, as many points allow, 2.62 with four).
 void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold) {
     int64_t items = 0, parts = 0, fold = 0;
     for (int32_t i = 0; i < n_img; ++i) {
@@ -327,13 +326,11 @@ void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part,
         m.nct = (m.nx + 15) / 16;
         m.ncb = (m.nct + kCT - 1) / kCT;
         m.nq = ((m.ny + 1) / 2 + 3) / 4;
-        const int64_t cells = static_cast<int64_t>(m.nkg) * m.ncb;
-        const int64_t want = (kVisWaves + cells - 1) / cells, most = (m.nq + 31) / 32;
-        m.nseg = static_cast<int32_t>(want < most ? want : most);
+        m.nseg = (m.nq + 31) / 32;
         m.item0 = static_cast<int32_t>(items);
         m.part0 = parts;
         m.fold0 = fold;
-        items += cells * m.nseg;
+        items += static_cast<int64_t>(m.nkg) * m.ncb * m.nseg;
         parts += static_cast<int64_t>(m.ncb) * m.nseg * m.K;
         fold += static_cast<int64_t>(m.nct) * m.nq * 128;
     }

@@ -170,3 +170,25 @@ def test_tile_edges(rt, orc, nx, ny, K):
         a, c = orc.visibility_rings(img, In, q, n_angles)
         assert np.abs(avg.cpu().numpy() - a).max() <= TOL
         assert np.abs(cut.cpu().numpy() - c).max() <= TOL
+
+
+@pytest.mark.parametrize("nx,ny,many", [(64, 600, 140000), (130, 1030, 70000), (333, 260, 40000)])
+def test_points_alone_and_among_many(rt, nx, ny, many):
+    """A point's amplitude and visibility are the same bits however many others the call has."""
+    import torch
+
+    img = W.image(metric="kerr", nx=nx, ny=ny)
+    I = torch.tensor(np.random.default_rng(nx).random((ny, nx)), device="cuda")
+    uv = torch.tensor(np.random.default_rng(ny).uniform(-0.5, 0.5, (many, 2)), device="cuda")
+
+    def run(points):
+        amp = torch.empty(len(points), dtype=torch.float64, device="cuda")
+        vis = torch.empty(len(points), 2, dtype=torch.float64, device="cuda")
+        rt.rt_visibility_dft(I, rt.params_from(img), points, amp, vis)
+        return amp, vis
+    say(f"{nx}x{ny}, {many} points")
+    amp, vis = run(uv)
+    for k in (1, 33, 500):
+        for first in (0, 5):
+            a, v = run(uv[first:first + k].contiguous())
+            assert torch.equal(a, amp[first:first + k]) and torch.equal(v, vis[first:first + k])
