@@ -362,9 +362,11 @@ int rt_set_kernel_timing(void *start_event, void *stop_event);
  *   amp        device [K] normalised amplitudes, or NULL
  *   vis        device [K][2] (Re V, Im V), or NULL (not both NULL)
  * Binary64 on the matrix cores, the phases generated in registers (no phase
- * table in memory); fixed summation order, deterministic.  Scratch (the image's
- * rows folded about its centre line, 16 bytes per point and partial sum, and a
- * few KB) is stream-ordered.  RT_ERR_ARG for a bad
+ * table in memory); fixed summation order, deterministic: a point's bits depend on
+ * the image and the point alone, not on K.  Scratch is stream-ordered: 16 bytes per
+ * point, block of 64 columns and segment of 256 rows, up to 256 MB (points beyond
+ * go in further launches; for screens of more than 2^19 blocks and segments at
+ * least what 32 points need), and some 2 KB per image.  RT_ERR_ARG for a bad
  * screen, K < 1 or K > 2^22. */
 int rt_visibility_dft(const double *intensity, const rt_image_params *params, const double *uv,
                       int32_t K, double *amp, double *vis, void *hip_stream);
@@ -397,8 +399,9 @@ int rt_visibility_dft_batch(const rt_vis_image *images, int32_t n_images, void *
  * angular harmonics below n_angles): avg[j] = mean_a |V(q_j cos phi_a,
  * q_j sin phi_a)| / |V(0,0)|; the cut is the amplitude at phi = 0:
  * cut[j] = |V(q_j, 0)| / |V(0,0)|.  avg and cut are device [n_q] or NULL (not
- * both).  Scratch (24 n_q n_angles bytes plus that of rt_visibility_dft) is
- * stream-ordered.  RT_ERR_ARG for null pointers, n_q or n_angles < 1 or
+ * both).  An even n_angles is summed over half of the circle, whose other half
+ * repeats its amplitudes.  Scratch (24 n_q n_angles bytes, half of it for an even
+ * n_angles, plus that of rt_visibility_dft for as many points) is stream-ordered.  RT_ERR_ARG for null pointers, n_q or n_angles < 1 or
  * n_q n_angles > 2^22, or a bad screen. */
 int rt_visibility_rings(const double *intensity, const rt_image_params *params, const double *q,
                         int32_t n_q, int32_t n_angles, double *avg, double *cut,

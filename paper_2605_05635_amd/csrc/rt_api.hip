@@ -933,10 +933,9 @@ int image_diagnostics_noalloc(const double* intensity, const rt_image_params* pa
 
 // Normalised visibility amplitudes of n images (rt_visibility_dft and its
 // batch form): validation, the work layout, one stream-ordered scratch block
-// (image table, flux partials, partial sums) and three kernel launches.
+// (entry table, flux partials, partial sums) and three kernel launches a round.
 int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
     std::vector<rt::VisImage> tab(n);
-    int32_t max_k = 0;
     for (int32_t i = 0; i < n; ++i) {
         const rt_vis_image& g = imgs[i];
         if (!g.intensity || !g.uv || (!g.amp && !g.vis))
@@ -961,7 +960,6 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
         m.dx = (g.x_max - g.x_min) / g.nx;
         m.y0 = g.y_min;
         m.dy = (g.y_max - g.y_min) / g.ny;
-        max_k = std::max(max_k, g.K);
     }
     for (int32_t i = 0; i < n; ++i) {
         const rt_vis_image& g = imgs[i];
@@ -975,16 +973,17 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
     int64_t blocks = 0;
     for (const rt::VisImage& m : tab)
         blocks += static_cast<int64_t>((m.K + 63) / 64) * ((m.nx + 15) / 16);
-    int64_t n_items = 0, n_part = 0, n_fold = 0;
-    rt::vis_layout(tab.data(), n, &n_items, &n_part, &n_fold);
-    if (blocks >= (int64_t(1) << 31) || n_items >= (int64_t(1) << 31))
-        return fail(RT_ERR_ARG, "too much visibility work for one call");
+    if (blocks >= (int64_t(1) << 31)) return fail(RT_ERR_ARG, "too much visibility work for one call");
+    std::vector<rt::VisImage> entries;
+    std::vector<rt::VisRound> rounds;
+    int64_t n_part = 0;
+    rt::vis_layout(tab.data(), n, &entries, &rounds, &n_part);
+    int32_t most = 0;   // entries of a round
+    for (const rt::VisRound& r : rounds) most = std::max(most, r.n);
     auto up256 = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t tab_bytes = up256(sizeof(rt::VisImage) * n);
-    const size_t flux_bytes = up256(sizeof(double) * rt::kVisFluxBlocks * n);
-    const size_t part_bytes = up256(sizeof(double2) * static_cast<size_t>(n_part));
-    const size_t fold_bytes = up256(sizeof(double) * static_cast<size_t>(n_fold));
-    const size_t bytes = tab_bytes + flux_bytes + part_bytes + fold_bytes;
+    const size_t tab_bytes = most > 1 ? up256(sizeof(rt::VisImage) * entries.size()) : 0;
+    const size_t flux_bytes = up256(sizeof(double) * rt::kVisFluxBlocks * most);
+    const size_t bytes = tab_bytes + flux_bytes + sizeof(double2) * static_cast<size_t>(n_part);
     void* mem = nullptr;
     hipError_t e = hipMallocAsync(&mem, bytes, stream);
     if (e != hipSuccess || !mem) {
@@ -996,22 +995,22 @@ int visibility_images(const rt_vis_image* imgs, int32_t n, hipStream_t stream) {
         (void)hipFreeAsync(mem, stream);
         return code;
     };
-    if (n > 1) {
+    if (most > 1) {
         void* host = nullptr;
-        const int rc = staging_reserve(sizeof(rt::VisImage) * n, &host);
+        const size_t used = sizeof(rt::VisImage) * entries.size();
+        const int rc = staging_reserve(used, &host);
         if (rc != RT_OK) return bail(rc);
-        std::memcpy(host, tab.data(), sizeof(rt::VisImage) * n);
-        if ((e = hipMemcpyAsync(base, host, sizeof(rt::VisImage) * n, hipMemcpyHostToDevice,
-                                stream)) != hipSuccess ||
+        std::memcpy(host, entries.data(), used);
+        if ((e = hipMemcpyAsync(base, host, used, hipMemcpyHostToDevice, stream)) != hipSuccess ||
             (e = hipEventRecord(g_staging.ready, stream)) != hipSuccess)
             return bail(hip_fail(e, "visibility table upload"));
     }
-    e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), tab[0], n,
-                              static_cast<int32_t>(n_items), max_k,
-                              reinterpret_cast<double2*>(base + tab_bytes + flux_bytes),
-                              reinterpret_cast<double*>(base + tab_bytes + flux_bytes + part_bytes),
-                              reinterpret_cast<double*>(base + tab_bytes), stream);
-    if (e != hipSuccess) return bail(hip_fail(e, "visibility kernel launch"));
+    for (const rt::VisRound& r : rounds) {
+        e = rt::launch_visibility(reinterpret_cast<const rt::VisImage*>(base), entries.data(), r,
+                                  reinterpret_cast<double2*>(base + tab_bytes + flux_bytes),
+                                  reinterpret_cast<double*>(base + tab_bytes), stream);
+        if (e != hipSuccess) return bail(hip_fail(e, "visibility kernel launch"));
+    }
     if ((e = hipFreeAsync(mem, stream)) != hipSuccess) return hip_fail(e, "hipFreeAsync");
     return RT_OK;
 }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 #include "rt_device.h"
 
@@ -117,15 +118,16 @@ constexpr int kReduceBlocks = 256;
 hipError_t launch_reduce(const ImageConst& c, const double* intensity, double* partials,
                          double* out, hipStream_t stream);
 
-// Normalised visibility amplitudes (Sec. 6.4) of n_img images in one launch
-// sequence.  VisImage holds one image (device pointers I [ny][nx], uv [K][2],
+// Normalised visibility amplitudes (Sec. 6.4) of many images.  VisImage holds one image (device pointers I [ny][nx], uv [K][2],
 // amp [K] or null, vis [K][2] or null; the screen of its pixel centres);
-// vis_layout fills the work split of a host table and its offsets and returns
-// the totals.  launch_visibility runs the row fold with the flux partials
-// (fold: n_fold doubles; fpart: kVisFluxBlocks doubles per image), the partial
-// sums (part: n_part double2) and the finish on the device copy d_tab of that
-// table, or for one image on `first` (the table's first, host) and no copy; max_k
-// is the largest K.  Deterministic.
+// vis_layout cuts a call's images into entries of rounds, which follow each other
+// on the stream and share one scratch of n_part partial sums: all points of all
+// images in one round where their partial sums fit kVisPart (256 MB), else as many
+// points as fit (at least one group of 32).  launch_visibility runs a round: the flux
+// partials (fpart: kVisFluxBlocks doubles per entry), the partial sums (part) and
+// the finish, on the device copy d_entries of the entries, or with a single entry on
+// `entries` (host) and no copy.  Deterministic; the rounds change no bits.
+constexpr int64_t kVisPart = int64_t(1) << 24;
 constexpr int kVisFluxBlocks = 256;   // flux partials per image
 struct VisImage {
     const double* I;
@@ -137,13 +139,17 @@ struct VisImage {
     int32_t nkg, ncb, nseg;           // point groups, column blocks, row segments
     int32_t item0;                    // first work item (wavefront) of the image
     int64_t part0;                    // first partial sum: [ncb nseg][K]
-    int64_t fold0;                    // first folded value: [nct][nq][2][64]
     double x0, dx, y0, dy;
 };
-void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold);
-hipError_t launch_visibility(const VisImage* d_tab, const VisImage& first, int32_t n_img, int32_t n_items,
-                             int32_t max_k, double2* part, double* fold, double* fpart,
-                             hipStream_t stream);
+struct VisRound {
+    int32_t first, n;                 // entries
+    int64_t n_items;
+    int32_t max_k;                    // most points of an entry
+};
+void vis_layout(const VisImage* imgs, int32_t n_img, std::vector<VisImage>* entries,
+                std::vector<VisRound>* rounds, int64_t* n_part);
+hipError_t launch_visibility(const VisImage* d_entries, const VisImage* entries, const VisRound& r, double2* part,
+                             double* fpart, hipStream_t stream);
 // Points on n_q rings (radius q[j], device), the first n_dirs of the angles
 // 2 pi a / n_angles: uv [n_q n_dirs][2]; and the average of amp over each
 // ring's n_dirs points (avg) with its amplitude at angle 0 (cut), either

@@ -12,19 +12,19 @@
 //   R_k(x) = sum_a cos(2 pi v_k a) S(a, x),   J_k(x) = sum_a sin(2 pi v_k a) D(a, x),
 // done on the matrix cores in binary64 (v_mfma_f64_16x16x4, which accumulates
 // with fused multiply-adds like the vector unit):
-//   * a first pass writes S and D in the order the matrix instructions read
-//     them (16 columns x 4 rows = one 512-byte load of a wavefront) and sums
-//     the flux |V(0,0)| on the way;
+//   * a first pass sums the flux |V(0,0)|;
 //   * one wavefront per work item = (image, 32 points, 64 columns, a segment
-//     of the folded rows), 16 accumulator tiles; a lane generates its own
-//     elements of the left operand, cos and sin of its point's phase at its
-//     row, stepped four rows by one complex multiplication and re-seeded from
-//     an exact sine and cosine every kReseed rows (recurrence error ~1e-14),
-//     in the shadow of the matrix instructions;
+//     of the folded rows), 16 accumulator tiles; a lane reads the pixel pairs of
+//     its own row and columns (a load of a wavefront is 16 columns x 4 rows) and
+//     generates its own elements of the left operand, cos and sin of its point's
+//     phase at its row, stepped four rows by one complex multiplication and
+//     re-seeded from an exact sine and cosine every kReseed row quads (recurrence
+//     error ~1e-14), in the shadow of the matrix instructions;
 //   * the item's 64 columns are then summed with exp(-2 pi i (u X + v Y_c)).
 // Each work item writes one partial sum per point; a last kernel adds a
 // point's partials in index order, scales by dX dY and divides by the flux.
 // Deterministic run to run, and the split of an image depends on its size alone.
+// Points go in rounds whose partial sums fit kVisPart, one round after another.
 //
 // Bound by the binary64 matrix rate: a probe of independent
 // v_mfma_f64_16x16x4 reaches 77 TFLOP/s on this card (71 with one wavefront
@@ -32,7 +32,9 @@
 // under the same power limit.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <vector>
 
 #include "rt_kernels.h"
 #include "rt_math.h"
@@ -59,16 +61,12 @@ __device__ __forceinline__ const VisImage& image_of(const VisImage* __restrict__
         return tab[i];
 }
 
-// Folded rows of an image in matrix-operand order: column tile t and row quad
-// q hold 64 values of S then 64 of D, value 16 r + c for row 4 q + r and column
-// 16 t + c (zero beyond the screen), which is the lane order of the right
-// operand.  Block b of image i takes every kVisFluxBlocks-th group of four
-// (tile, quad) cells and leaves the sum of its S values, a partial of the
-// flux, in fpart[i kVisFluxBlocks + b] (fixed order).
+// Flux partials, over cells of 16 columns x 4 row pairs: block b of image i takes
+// every kVisFluxBlocks-th group of four cells and leaves their sum in
+// fpart[i kVisFluxBlocks + b] (fixed order).
 template <bool ONE>
-__global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* __restrict__ tab,
-                                                               VisImage one, double* __restrict__ fold,
-                                                               double* __restrict__ fpart) {
+__global__ __launch_bounds__(kVisThreads) void vis_flux_kernel(const VisImage* __restrict__ tab,
+                                                               VisImage one, double* __restrict__ fpart) {
     __shared__ double sh[kVisThreads];
     const VisImage& m = image_of<ONE>(tab, one, static_cast<int>(blockIdx.y));
     const int32_t nx = m.nx, ny = m.ny, nq = m.nq;
@@ -80,21 +78,12 @@ __global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* _
          cell += 4 * kVisFluxBlocks) {
         const int32_t t = static_cast<int32_t>(cell / nq), q = static_cast<int32_t>(cell - static_cast<int64_t>(t) * nq);
         const int32_t x = 16 * t + col, y = 4 * q + r;
-        double S = 0.0, D = 0.0;
+        double S = 0.0;
         if (x < nx && y < h) {
             const int32_t z = ny - 1 - y;
-            const double a = m.I[static_cast<int64_t>(y) * nx + x];
-            if (z > y) {
-                const double b = m.I[static_cast<int64_t>(z) * nx + x];
-                S = a + b;
-                D = a - b;
-            } else {
-                S = a;   // the centre row of an odd screen
-            }
+            S = m.I[static_cast<int64_t>(y) * nx + x];
+            if (z > y) S += m.I[static_cast<int64_t>(z) * nx + x];   // (else the centre row of an odd screen)
         }
-        double* out = fold + m.fold0 + cell * 128 + lane;
-        out[0] = S;
-        out[64] = D;
         sum += S;
     }
     sh[threadIdx.x] = sum;
@@ -110,7 +99,7 @@ __global__ __launch_bounds__(kVisThreads) void vis_fold_kernel(const VisImage* _
 template <bool ONE>
 __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void vis_partial_kernel(
     const VisImage* __restrict__ tab, VisImage one, int32_t n_img, int32_t n_items,
-    const double* __restrict__ fold, double2* __restrict__ part) {
+    double2* __restrict__ part) {
     const int32_t w = __builtin_amdgcn_readfirstlane(
         static_cast<int32_t>(blockIdx.x) * (kVisThreads / 64) + static_cast<int32_t>(threadIdx.x >> 6));
     if (w >= n_items) return;
@@ -128,7 +117,6 @@ __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 
     const int lane = __lane_id(), r = lane >> 4, i16 = lane & 15;
     const int32_t q0 = static_cast<int32_t>(static_cast<int64_t>(nq) * seg / m.nseg);
     const int32_t q1 = static_cast<int32_t>(static_cast<int64_t>(nq) * (seg + 1) / m.nseg);
-    const int32_t ct = m.nct - cb * kCT < kCT ? m.nct - cb * kCT : kCT;   // column tiles of this item
     const int32_t k0 = kg * 16 * kPT;
 
     // left operand: lane (r, i16) holds point k0 + 16 p + i16 at row 4 q + r
@@ -147,29 +135,48 @@ __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
         for (int t = 0; t < kCT; ++t) R[p][t] = J[p][t] = Acc{0.0, 0.0, 0.0, 0.0};
 
-    const double* f = fold + m.fold0 + (static_cast<int64_t>(cb) * kCT * nq + q0) * 128 + lane;
-    const int64_t tile = static_cast<int64_t>(nq) * 128;
-    const double half = 0.5 * static_cast<double>(m.ny);
-    double S[kCT], D[kCT];
+    // right operand: the pair of rows y = 4 q + r and ny - 1 - y at column 64 cb +
+    // 16 t + i16; rows and columns beyond the screen (clamped here) enter as zeros
+    const int32_t nx = m.nx, ny = m.ny, h = (ny + 1) / 2;
+    int32_t col[kCT];
+    bool inside[kCT];
 #pragma unroll
     for (int t = 0; t < kCT; ++t) {
-        S[t] = t < ct ? f[t * tile] : 0.0;
-        D[t] = t < ct ? f[t * tile + 64] : 0.0;
+        const int32_t x = 16 * (cb * kCT + t) + i16;
+        inside[t] = x < nx;
+        col[t] = inside[t] ? x : nx - 1;
     }
+    double a[kCT], b[kCT];
+    auto load = [&](int32_t q) {
+        const int32_t y = 4 * q + r, yc = y < h ? y : h - 1;
+        const double* top = m.I + static_cast<int64_t>(yc) * nx;
+        const double* bottom = m.I + static_cast<int64_t>(ny - 1 - yc) * nx;
+#pragma unroll
+        for (int t = 0; t < kCT; ++t) {
+            a[t] = top[col[t]];
+            b[t] = bottom[col[t]];
+        }
+    };
+    const double half = 0.5 * static_cast<double>(ny);
+    load(q0);
     for (int32_t q = q0; q < q1; ++q) {
         if (((q - q0) & (kReseed - 1)) == 0) {
 #pragma unroll
             for (int p = 0; p < kPT; ++p)
                 dm::sincos(tv[p] * ((static_cast<double>(4 * q + r) + 0.5 - half) * m.dy), &s[p], &c[p]);
         }
-        // the next quad's loads stay in flight under this quad's products
-        double Sn[kCT], Dn[kCT];
-        f += q + 1 < q1 ? 128 : 0;
+        // (the centre row of an odd screen has no partner)
+        const int32_t y = 4 * q + r;
+        const bool row = y < h, pair = y < ny - 1 - y;
+        double S[kCT], D[kCT];
 #pragma unroll
         for (int t = 0; t < kCT; ++t) {
-            Sn[t] = t < ct ? f[t * tile] : 0.0;
-            Dn[t] = t < ct ? f[t * tile + 64] : 0.0;
+            const double s_ = pair ? a[t] + b[t] : a[t], d_ = a[t] - b[t];
+            S[t] = row && inside[t] ? s_ : 0.0;
+            D[t] = pair && inside[t] ? d_ : 0.0;
         }
+        // the next quad's loads stay in flight under this quad's products
+        load(q + 1 < q1 ? q + 1 : q);
 #pragma unroll
         for (int p = 0; p < kPT; ++p)
 #pragma unroll
@@ -182,11 +189,6 @@ __global__ __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(2, 
             const double cn = c[p] * wc[p] - s[p] * ws[p];
             s[p] = s[p] * wc[p] + c[p] * ws[p];
             c[p] = cn;
-        }
-#pragma unroll
-        for (int t = 0; t < kCT; ++t) {
-            S[t] = Sn[t];
-            D[t] = Dn[t];
         }
     }
     // Columns.  Element v of a result tile is point r + 4 v of the point tile
@@ -318,49 +320,69 @@ __global__ void ring_average_kernel(const double* __restrict__ amp, int32_t n_q,
 // segment for every 32 quads (256 image rows) or part of it.  The split is the
 // image's, whatever the number of points, and with it a point's bits (1024^2, 60,000
 // points: 2.47 ms with one segment, as many points allow, 2.62 with four).
-void vis_layout(VisImage* tab, int32_t n_img, int64_t* n_items, int64_t* n_part, int64_t* n_fold) {
-    int64_t items = 0, parts = 0, fold = 0;
+void vis_layout(const VisImage* imgs, int32_t n_img, std::vector<VisImage>* entries,
+                std::vector<VisRound>* rounds, int64_t* n_part) {
+    entries->clear();
+    rounds->assign(1, VisRound{0, 0, 0, 0});
+    int64_t part = 0, most = 0;   // partial sums of the last round, of the largest
     for (int32_t i = 0; i < n_img; ++i) {
-        VisImage& m = tab[i];
-        m.nkg = (m.K + 16 * kPT - 1) / (16 * kPT);
+        VisImage m = imgs[i];
         m.nct = (m.nx + 15) / 16;
         m.ncb = (m.nct + kCT - 1) / kCT;
         m.nq = ((m.ny + 1) / 2 + 3) / 4;
         m.nseg = (m.nq + 31) / 32;
-        m.item0 = static_cast<int32_t>(items);
-        m.part0 = parts;
-        m.fold0 = fold;
-        items += static_cast<int64_t>(m.nkg) * m.ncb * m.nseg;
-        parts += static_cast<int64_t>(m.ncb) * m.nseg * m.K;
-        fold += static_cast<int64_t>(m.nct) * m.nq * 128;
+        const int64_t cells = static_cast<int64_t>(m.ncb) * m.nseg;
+        for (int32_t left = m.K; left > 0;) {
+            VisRound& r = rounds->back();
+            const int64_t fit = (kVisPart - part) / cells;
+            if (left <= fit)
+                m.K = left;
+            else if (fit >= 16 * kPT || r.n == 0)
+                m.K = std::min<int32_t>(left, fit < 16 * kPT ? 16 * kPT : static_cast<int32_t>(fit / (16 * kPT)) * 16 * kPT);
+            else {
+                rounds->push_back(VisRound{static_cast<int32_t>(entries->size()), 0, 0, 0});
+                part = 0;
+                continue;
+            }
+            m.nkg = (m.K + 16 * kPT - 1) / (16 * kPT);
+            m.item0 = static_cast<int32_t>(r.n_items);
+            m.part0 = part;
+            entries->push_back(m);
+            ++r.n;
+            r.n_items += m.nkg * cells;
+            r.max_k = std::max(r.max_k, m.K);
+            part += cells * m.K;
+            most = std::max(most, part);
+            left -= m.K;
+            m.uv += 2 * static_cast<int64_t>(m.K);
+            if (m.amp) m.amp += m.K;
+            if (m.vis) m.vis += 2 * static_cast<int64_t>(m.K);
+        }
     }
-    *n_items = items;
-    *n_part = parts;
-    *n_fold = fold;
+    *n_part = most;
 }
 
 template <bool ONE>
-static void launch_all(const VisImage* tab, const VisImage& one, int32_t n_img, int32_t n_items,
-                       int32_t max_k, double2* part, double* fold, double* fpart, hipStream_t stream) {
-    hipLaunchKernelGGL(vis_fold_kernel<ONE>, dim3(kVisFluxBlocks, static_cast<unsigned>(n_img)),
-                       dim3(kVisThreads), 0, stream, tab, one, fold, fpart);
+static void launch_all(const VisImage* tab, const VisImage& one, const VisRound& r, double2* part, double* fpart,
+                       hipStream_t stream) {
+    hipLaunchKernelGGL(vis_flux_kernel<ONE>, dim3(kVisFluxBlocks, static_cast<unsigned>(r.n)),
+                       dim3(kVisThreads), 0, stream, tab, one, fpart);
     const int32_t per_block = kVisThreads / 64;
     hipLaunchKernelGGL(vis_partial_kernel<ONE>,
-                       dim3((static_cast<unsigned>(n_items) + per_block - 1) / per_block),
-                       dim3(kVisThreads), 0, stream, tab, one, n_img, n_items, fold, part);
+                       dim3(static_cast<unsigned>((r.n_items + per_block - 1) / per_block)),
+                       dim3(kVisThreads), 0, stream, tab, one, r.n, static_cast<int32_t>(r.n_items), part);
     hipLaunchKernelGGL(vis_finish_kernel<ONE>,
-                       dim3(static_cast<unsigned>((max_k + kVisThreads - 1) / kVisThreads),
-                            static_cast<unsigned>(n_img)),
+                       dim3(static_cast<unsigned>((r.max_k + kVisThreads - 1) / kVisThreads),
+                            static_cast<unsigned>(r.n)),
                        dim3(kVisThreads), 0, stream, tab, one, part, fpart);
 }
 
-hipError_t launch_visibility(const VisImage* d_tab, const VisImage& first, int32_t n_img, int32_t n_items,
-                             int32_t max_k, double2* part, double* fold, double* fpart,
-                             hipStream_t stream) {
-    if (n_img == 1)
-        launch_all<true>(nullptr, first, 1, n_items, max_k, part, fold, fpart, stream);
+hipError_t launch_visibility(const VisImage* d_entries, const VisImage* entries, const VisRound& r, double2* part,
+                             double* fpart, hipStream_t stream) {
+    if (r.n == 1)
+        launch_all<true>(nullptr, entries[r.first], r, part, fpart, stream);
     else
-        launch_all<false>(d_tab, first, n_img, n_items, max_k, part, fold, fpart, stream);
+        launch_all<false>(d_entries + r.first, entries[r.first], r, part, fpart, stream);
     return hipGetLastError();
 }
 

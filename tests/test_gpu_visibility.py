@@ -192,3 +192,25 @@ def test_points_alone_and_among_many(rt, nx, ny, many):
         for first in (0, 5):
             a, v = run(uv[first:first + k].contiguous())
             assert torch.equal(a, amp[first:first + k]) and torch.equal(v, vis[first:first + k])
+
+
+def test_rounds_of_many_points(rt):
+    """More points than one round's scratch holds: the same bits as in calls of a few."""
+    import torch
+
+    img = W.image(metric="kerr", nx=70, ny=2100)
+    I = torch.tensor(np.random.default_rng(7).random((2100, 70)), device="cuda")
+    n = (1 << 24) // 18 + 100   # two column blocks, nine segments
+    uv = torch.tensor(np.random.default_rng(8).uniform(-0.5, 0.5, (n, 2)), device="cuda")
+    say(f"70x2100, {n} points")
+    amp = torch.full((n,), -1.0, dtype=torch.float64, device="cuda")
+    vis = torch.empty(n, 2, dtype=torch.float64, device="cuda")
+    rt.rt_visibility_dft(I, rt.params_from(img), uv, amp, vis)
+    assert float(amp.min()) >= 0.0
+    for k in (0, n - 150, n // 2):
+        a, v = torch.empty(150, dtype=torch.float64, device="cuda"), torch.empty(150, 2, dtype=torch.float64, device="cuda")
+        rt.rt_visibility_dft(I, rt.params_from(img), uv[k:k + 150].contiguous(), a, v)
+        assert torch.equal(a, amp[k:k + 150]) and torch.equal(v, vis[k:k + 150])
+    # images that share a round with others, and one of a round of its own
+    amps = rt.visibility_many([img, img, img], [I, I, I], [uv[:400000], uv, uv[5:900]])
+    assert torch.equal(amps[0], amp[:400000]) and torch.equal(amps[1], amp) and torch.equal(amps[2], amp[5:900])
