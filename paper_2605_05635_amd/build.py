@@ -15,6 +15,9 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libgeodesic_rt.so")
+# the device checks of the tests: the headers' functions on given arguments
+CHECKS_SRC = os.path.join(ROOT, "tests", "device", "device_checks.hip")
+CHECKS_LIB = os.path.join(ROOT, "tests", "device", "libdevice_checks.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed FP32 instructions are disabled for all device code: the compiler
@@ -33,17 +36,24 @@ DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang"
 CODEGEN_FLAGS = ["-mllvm", "-disable-machine-licm", "-ffp-contract=on"]
 
 
-def build(verbose: bool = False, extra: list[str] | None = None) -> str:
-    srcs = sorted(glob.glob(os.path.join(PKG, "csrc", "*.hip")))
+def _compile(srcs: list[str], lib: str, verbose: bool, extra: list[str] | None) -> str:
     cmd = [HIPCC, *DEVICE_FLAGS, *CODEGEN_FLAGS, "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-           *(extra or []), "-o", LIB + ".tmp", *srcs,
+           *(extra or []), "-o", lib + ".tmp", *srcs,
            "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    os.replace(LIB + ".tmp", LIB)
-    return LIB
+    os.replace(lib + ".tmp", lib)
+    return lib
+
+
+def build(verbose: bool = False, extra: list[str] | None = None) -> str:
+    return _compile(sorted(glob.glob(os.path.join(PKG, "csrc", "*.hip"))), LIB, verbose, extra)
+
+
+def build_checks(verbose: bool = False) -> str:
+    return _compile([CHECKS_SRC], CHECKS_LIB, verbose, None)
 
 
 if __name__ == "__main__":

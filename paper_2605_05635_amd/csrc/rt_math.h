@@ -122,10 +122,11 @@ __host__ __device__ inline double rsqrt(double x) {
 #endif
 }
 
-// sqrt(x) for x = 0, x >= 2^-767 or +infinity: the compiler's correctly rounded
-// sequence (a Goldschmidt step from the hardware estimate of 1/sqrt, two
-// residual corrections) without the scaling that serves smaller arguments,
-// eight of its 22 instructions.
+// sqrt(x), correctly rounded, for x = 0, x >= 2^-767 or +infinity: a step of
+// Goldschmidt's iteration (R. E. Goldschmidt, 1964) from the hardware estimate of
+// 1/sqrt, then two residual corrections by fused multiply-adds (P. W. Markstein,
+// IBM J. Res. Dev. 34, 1990), without the scaling that smaller arguments need for
+// their residuals (eight of the 22 instructions of a square root).
 __host__ __device__ inline double sqrt_normal(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const double y = __builtin_amdgcn_rsq(x);

@@ -486,7 +486,11 @@ __host__ __device__ __forceinline__ double crossing_root(const DenseComp& d, boo
 // R, its u^T from u.u = -1 with the metric at (R, theta) (eqs. (89)-(90)); no
 // emission where that has no solution.  The quotients go through reciprocals
 // of their denominators (g^3 = A^(3/2) (1/den)^3).  The early returns stay:
-// a branch-free version kept more values live and spilled.
+// a branch-free version kept more values live and spilled.  The arguments of the
+// roots are 0 or far above 2^-767: A and dF - 2 F/R are sums of terms of which the
+// largest is 2^-53 or more (mu of the Einasto seed is 0 or at least 2^-54, the other
+// terms are of order one), so what cancellation leaves is 0 or at least 2^-160, and
+// the disc's window ends far below R = 10^90, where 1/R^2 would matter.
 template <class T>
 __host__ __device__ inline double thick_source(const Hot& k, double R, double s, double co, double F,
                                                double dF, double E, double L, const T& tb) {

@@ -2,8 +2,10 @@
 // the outer horizon as the largest root of Delta(R) = R^2 - F(R) + chi^2
 // (eq. (33)), the ergosurface as the largest root with chi^2 cos^2(theta) in
 // place of chi^2 (g_TT = 0), and the extremal spin chi_e^2 = max_R (F(R) -
-// R^2), beyond which Delta has no root.  Host and device (the image set-up
-// and the parameter-scan kernel use the same code).
+// R^2), beyond which Delta has no root.  Host and device.  The image set-up runs
+// largest_root; the parameter-scan kernel (rt_scan.hip) evaluates the intervals that
+// can matter of the same grids, to the same bits, which a test compares with these
+// searches on the device.
 #pragma once
 
 #include "rt_device.h"

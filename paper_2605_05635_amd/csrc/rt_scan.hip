@@ -21,7 +21,7 @@
 // 4096 points of the cored NFW: 796 -> 29 us; the results' bits, NaNs included,
 // are those of the evaluation of every interval.
 #include "rt.h"
-#include "rt_scan.h"
+#include "rt_device.h"
 
 namespace rt {
 namespace {

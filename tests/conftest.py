@@ -21,6 +21,19 @@ def orc():
     return O
 
 
+@pytest.fixture(scope="session")
+def device_checks():
+    """The device checks (tests/device, built with the library or on first use)."""
+    import ctypes
+
+    import torch   # first: the library then uses the HIP runtime that torch brings, not another
+    assert torch.cuda.is_available(), "GPU test run without a GPU"
+    from paper_2605_05635_amd import build
+    if not os.path.exists(build.CHECKS_LIB):
+        build.build_checks()
+    return ctypes.CDLL(build.CHECKS_LIB)
+
+
 def oracle_einasto_extremal_spin(lam_e: float) -> float:
     """The extremal spin of the Einasto seed from the oracle (0 without one)."""
     from oracle import oracle as O
