@@ -315,8 +315,9 @@ int rt_refine_points(const rt_image_params *params, const uint8_t *ncross, const
  *     inside below the transition and escaping above it;
  *   - a direction in which a traced ray is out of order, or runs out of attempts
  *     or ends by a non-finite estimate, goes on by passes of single levels, from the
- *     last bracket that such passes reached unless what is out of order lies 16
- *     times its extent inside the bracket at hand;
+ *     last bracket that such passes reached; after rays out of order from the
+ *     bracket at hand if the edges left out, as far as 256 times the extent of what
+ *     is out of order, are traced and end as it supposes;
  *   - where rays out of order were all left out, the bracket can be at another
  *     transition within the integration's error of the first (none of 690,000
  *     directions at tolerances of 1e-8 and 1e-7 was).

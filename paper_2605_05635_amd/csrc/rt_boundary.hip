@@ -14,9 +14,8 @@
 // rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 21.7 ms by uniform
 // passes, 14.7 by guided ones (five to seven passes in place of nine); 500 at S = 64:
 // 14.0 and 9.7 ms.
-// What is left is the longest direction's chain, 5924 attempts of 2.4 us; 21 ms in
-// one call of ten, where some direction came out of order, and over 40 in one of
-// thirty, where it started again from its uniform bracket (search::redo).
+// What is left is the longest direction's chain, 5924 attempts of 2.4 us; 21 to 40
+// ms in one call of ten, where some direction came out of order (search::redo).
 #include "rt_ray.h"
 #include "rt_search.h"
 
@@ -67,7 +66,7 @@ struct GroupLanes {
 // radial time nor the nearest samples (with both kinds in one kernel, uniform
 // searches took 3 to 6 % longer: Kerr at a tolerance of 1e-5 5.64 -> 5.37 ms).  Registers as the trace kernel's, the
 // tableau not pinned; the guided kernels of Einasto and of the near cored NFW
-// spill 22 and 26 of them, in the code between passes.
+// spill 30 and 33 of them, in the code between passes.
 template <int METRIC, bool GUIDED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void boundary_kernel(
     ImageConst c, const double* __restrict__ dirs, int32_t n, int32_t S, double b_lo, double b_hi,

@@ -38,17 +38,17 @@ constexpr int kMay = 1, kDid = 2;   // a direction may run guided passes, has ru
 // five passes for 3294 of them and in six or seven for the others, against 2823
 // without it (0.25: 3143, 0.7: 3120; the same order in four other spacetimes).
 constexpr double kBias = 0.45;
-// How far from a bracket's ends rays out of order have to lie for it to stand, in
-// units of their own extent (redo).
-constexpr double kFar = 16.0;
+// How far from rays out of order others may be, in units of the extent of those that
+// have been seen (redo).
+constexpr double kFar = 256.0;
 
 // What a direction keeps between passes: its two nearest escaping samples with
 // their radial times (b_c < e1 < e2; infinity where there is none), its two
-// nearest captured ones (c2 < c1 < b_c; minus infinity), its bracket, and the
-// last one that uniform passes alone had reached, with its level.
+// nearest captured ones (c2 < c1 < b_c; minus infinity), its bracket, the last one
+// that uniform passes alone had reached, with its level, and the range of a check.
 struct Nearest {
     double e1, te1, e2, te2, c1, tc1, c2, tc2;
-    double lo, hi, ulo, uhi;
+    double lo, hi, ulo, uhi, from, to;
     int ulevel;
 };
 
@@ -57,6 +57,7 @@ struct Course {
     int level;     // levels of the multisection done (-1: bracket unchecked)
     int guide;     // kMay, kDid
     bool guided;   // the next pass is a guided one
+    int check;     // edges of the bracket checked (-1: no check under way)
     bool done;
 };
 
@@ -84,6 +85,16 @@ __host__ __device__ __forceinline__ double edge(double lo, double hi, double w, 
     if (j > S) return hi;
     const double t = static_cast<double>(j) * w;
     return lo + t;
+}
+
+// The first edge j = 1..S + 1 that is not below e (e above lo, at most hi).
+__host__ __device__ __forceinline__ int first_edge(double lo, double hi, double w, double e, int S) {
+    const double r = (e - lo) / w;
+    int j = r >= static_cast<double>(S) ? S : static_cast<int>(r) - 1;
+    if (j < 1) j = 1;
+    while (j <= S && edge(lo, hi, w, j, S) < e) ++j;
+    while (j > 1 && edge(lo, hi, w, j - 1, S) >= e) --j;
+    return j;
 }
 
 // Cell j = 1..S + 1 of (lo, hi, w).
@@ -139,7 +150,29 @@ __host__ __device__ __forceinline__ void begin(const Search& q, N& n, Course& s)
     s.level = -1;
     s.guide = kMay;
     s.guided = false;
+    s.check = -1;
     s.done = false;
+}
+
+// Sample `at` of the check of (n.lo, n.hi): the edges that decide the levels from
+// (n.ulo, n.uhi) down to it, of each up to the first that is to escape, within
+// n.from..n.to.  Below the bracket's upper end they end inside and from there they
+// escape, if it is multisection's.  Not traced past the last of them.
+template <class N>
+__host__ __device__ __forceinline__ Sample check_edge(const Search& q, int at, const N& n, const Course& s) {
+    const double hi = n.hi, from = n.from, to = n.to;
+    double l = n.ulo, h = n.uhi;
+    const int levels = s.level - n.ulevel;
+    for (int m = 0; m < levels; ++m) {
+        const double w = (h - l) / (q.S + 1);
+        const int j = first_edge(l, h, w, hi, q.S), first = from > l ? first_edge(l, h, w, from, q.S) : 1;
+        int last = j < q.S ? j : q.S;
+        if (last >= first && !(edge(l, h, w, last, q.S) <= to)) --last;   // (the others are below the bracket)
+        if (first + at <= last) return Sample{edge(l, h, w, first + at, q.S), 0.0, true, 0};
+        if (last >= first) at -= last - first + 1;
+        cell(l, h, w, j, q.S);
+    }
+    return Sample{0.0, 0.0, false, 0};
 }
 
 // Lane sl's sample of the next pass along a direction of this length (b times it is
@@ -157,6 +190,7 @@ __host__ __device__ __forceinline__ Sample choose(const Search& q, double length
         p.traced = sl < 2;
         return p;
     }
+    if (s.check >= 0) return check_edge(q, s.check + sl, n, s);
     // The finest level, at most three down, whose cells the prediction
     // is expected to miss by no more than S / 4.
     const double W = (hi - lo) * length;
@@ -214,20 +248,28 @@ __host__ __device__ __forceinline__ void keep_two(double v, double t, D& a, D& t
     }
 }
 
+// Back to the last bracket that uniform passes had reached.
+template <class N>
+__host__ __device__ __forceinline__ void restart(N& n, Course& s) {
+    n.lo = n.ulo;
+    n.hi = n.uhi;
+    s.level = n.ulevel;
+}
+
 // Whether a finished pass's samples are dropped.  The edges that guided passes
 // leave out do not matter as long as fates are in order, captured below the
 // transition and escaping above.  A sample that ended inside above one that
 // escaped is out of order (below `finest` passes are uniform in any case): the
-// direction goes on by uniform passes.  From the bracket that it had, if what is
-// out of order lies well inside, kFar times its extent from either end: every edge
-// that guided passes left out is at those ends or outside.  Else, or after a ray
-// that ran out of attempts or whose error estimate was not finite (it counts as
-// inside wherever it is), from the last bracket that uniform passes had reached.
-// 150 calls of 4096 directions took 17.3 ms in the mean and 41 to 51 at most (16.5
-// and 28 from the bracket they had always, 18.2 in the mean from the uniform one
-// always), with the same brackets.  On scripted rays whose transition jumps hundreds
-// of times within the jump's size, 208 directions of 89,875 ended beside multisection's
-// bracket from the bracket they had, 5 with this rule.
+// direction goes on by uniform passes from the bracket that it had, if those of
+// the edges left out that lie within kFar times the extent of what is out of order
+// turn out as the bracket supposes.  Else, or after a ray that ran out of attempts
+// or whose error estimate was not finite (it counts as inside wherever it is), from
+// the last bracket that uniform passes had reached.
+//   200 calls of 4096 directions (cored NFW): mean 16.7 ms and largest 28 without
+// the check, 17.2 and 40 with it, 18.2 and 47 from the uniform bracket always; the
+// same brackets.  On scripted rays whose transition jumps hundreds of times within
+// the jumps' size, 208, 20 and none of 89,875 such directions ended beside
+// multisection's bracket; where the jumps are farther apart, none.
 template <class Lanes, class N>
 __host__ __device__ __forceinline__ bool redo(const Search& q, const Lanes& lanes, N& n, Course& s) {
     double out_b, in_b, unused;
@@ -250,11 +292,9 @@ __host__ __device__ __forceinline__ bool redo(const Search& q, const Lanes& lane
     s.guide = 0;
     if (drop) {
         const double far = kFar * (in_b - out_b);
-        if (lost || !(out_b - far > n.lo && in_b + far < n.hi)) {
-            n.lo = n.ulo;
-            n.hi = n.uhi;
-            s.level = n.ulevel;
-        }
+        n.from = out_b - far;
+        n.to = in_b + far;
+        if (lost) restart(n, s); else s.check = 0;
         n.e1 = n.e2 = INFINITY;
         n.c1 = n.c2 = -INFINITY;
     }
@@ -266,6 +306,13 @@ __host__ __device__ __forceinline__ bool redo(const Search& q, const Lanes& lane
 template <class Lanes, class N>
 __host__ __device__ __forceinline__ void narrow(const Search& q, const Lanes& lanes, N& n, Course& s) {
     const int S = q.S;
+    if (s.check >= 0) {
+        const double hi = n.hi;
+        const bool other = lanes.any([&](const Sample& p) { return p.traced && (p.fate == RAY_ESCAPED) != (p.b >= hi); });
+        if (other) restart(n, s);
+        s.check = other || lanes.any([](const Sample& p) { return !p.traced; }) ? -1 : s.check + S;
+        return;
+    }
     if (redo(q, lanes, n, s)) {
         s.guided = false;
         return;
@@ -310,11 +357,7 @@ __host__ __device__ __forceinline__ void narrow(const Search& q, const Lanes& la
     // the levels that (c1, e1) settles: no edge strictly inside it
     while (!s.done) {
         const double w = (hi - lo) / (S + 1);
-        const double r = (e1 - lo) / w;
-        int j = r >= static_cast<double>(S) ? S : static_cast<int>(r) - 1;
-        if (j < 1) j = 1;
-        while (j <= S && edge(lo, hi, w, j, S) < e1) ++j;
-        while (j > 1 && edge(lo, hi, w, j - 1, S) >= e1) --j;
+        const int j = first_edge(lo, hi, w, e1, S);
         if (!(edge(lo, hi, w, j - 1, S) <= c1)) break;
         double nlo = lo, nhi = hi;
         cell(nlo, nhi, w, j, S);
