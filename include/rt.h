@@ -316,7 +316,7 @@ int rt_refine_points(const rt_image_params *params, const uint8_t *ncross, const
  *   - a direction in which a traced ray is out of order, or runs out of attempts
  *     or ends by a non-finite estimate, goes on by passes of single levels, from the
  *     last bracket that such passes reached; after rays out of order from the
- *     bracket at hand if the edges left out, as far as 256 times the extent of what
+ *     bracket at hand if the edges left out, as far as 16 times the extent of what
  *     is out of order, are traced and end as it supposes;
  *   - where rays out of order were all left out, the bracket can be at another
  *     transition within the integration's error of the first (none of 690,000

@@ -14,7 +14,7 @@
 // rays end.  4096 directions at S = 16, cored NFW chi = 0.94: 21.7 ms by uniform
 // passes, 14.7 by guided ones (five to seven passes in place of nine); 500 at S = 64:
 // 14.0 and 9.7 ms.
-// What is left is the longest direction's chain, 5924 attempts of 2.4 us; 21 to 40
+// What is left is the longest direction's chain, 5924 attempts of 2.4 us; 21 to 32
 // ms in one call of ten, where some direction came out of order (search::redo).
 #include "rt_ray.h"
 #include "rt_search.h"

@@ -40,7 +40,7 @@ constexpr int kMay = 1, kDid = 2;   // a direction may run guided passes, has ru
 constexpr double kBias = 0.45;
 // How far from rays out of order others may be, in units of the extent of those that
 // have been seen (redo).
-constexpr double kFar = 256.0;
+constexpr double kFar = 16.0;
 
 // What a direction keeps between passes: its two nearest escaping samples with
 // their radial times (b_c < e1 < e2; infinity where there is none), its two
@@ -266,10 +266,11 @@ __host__ __device__ __forceinline__ void restart(N& n, Course& s) {
 // or whose error estimate was not finite (it counts as inside wherever it is), from
 // the last bracket that uniform passes had reached.
 //   200 calls of 4096 directions (cored NFW): mean 16.7 ms and largest 28 without
-// the check, 17.2 and 40 with it, 18.2 and 47 from the uniform bracket always; the
-// same brackets.  On scripted rays whose transition jumps hundreds of times within
-// the jumps' size, 208, 20 and none of 89,875 such directions ended beside
-// multisection's bracket; where the jumps are farther apart, none.
+// the check, 16.9 and 32 with it, 17.2 and 40 with 256 extents, 18.2 and 47 from the
+// uniform bracket always; the same brackets.  On scripted rays whose transition jumps
+// hundreds of times within the jumps' size, 208, 52, 20 and none of 89,875 such
+// directions ended beside multisection's bracket; where the jumps are farther
+// apart, none.
 template <class Lanes, class N>
 __host__ __device__ __forceinline__ bool redo(const Search& q, const Lanes& lanes, N& n, Course& s) {
     double out_b, in_b, unused;

@@ -4,7 +4,7 @@
 // A ray at b escapes above b_c + shift(b), a step function of b as an accept or reject decision that flips
 // between neighbouring rays makes it: on each interval of length `period` another value within +-jump.  Within
 // `lost` of b_c it runs out of attempts with probability 1/4.  `length` is the direction's.
-//   out: lo, hi, passes, the samples traced, whether a pass was dropped
+//   out: lo, hi, passes, the samples traced, whether a pass was dropped, the range that was checked then
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -69,7 +69,7 @@ int main() {
         search::Course course;
         search::begin(q, near, course);
         std::vector<search::Sample> lanes(static_cast<size_t>(q.S));
-        double passes = 0.0, traced = 0.0, dropped = 0.0;
+        double passes = 0.0, traced = 0.0, dropped = 0.0, from = -INFINITY, to = INFINITY;
         course.level = 0;
         while (!course.done) {
             for (int sl = 0; sl < q.S; ++sl) {
@@ -83,8 +83,12 @@ int main() {
             const bool did = course.guide & search::kDid;
             search::narrow(q, ArrayLanes{lanes}, near, course);
             if (did && course.guide == 0) dropped = 1.0;
+            if (course.check >= 0) {
+                from = near.from;
+                to = near.to;
+            }
         }
-        for (double v : {near.lo, near.hi, passes, traced, dropped}) out.push_back(v);
+        for (double v : {near.lo, near.hi, passes, traced, dropped, from, to}) out.push_back(v);
     }
     std::fwrite(out.data(), sizeof(double), out.size(), stdout);
     return 0;

@@ -23,7 +23,7 @@ def driver(tmp_path_factory):
     def run(rows):
         rows = np.ascontiguousarray(rows, dtype=np.float64)
         out = subprocess.run([exe], input=rows.tobytes(), capture_output=True, check=True).stdout
-        return np.frombuffer(out).reshape(len(rows), 5)
+        return np.frombuffer(out).reshape(len(rows), 7)
     return run
 
 
@@ -78,18 +78,21 @@ def test_in_order(driver, S, b_tol):
 @pytest.mark.parametrize("jump,period,lost", [(1e-9, 1e-9, 0.0), (1e-8, 3e-9, 0.0), (1e-7, 1e-7, 0.0), (1e-6, 3e-7, 0.0),
                                               (1e-5, 1e-5, 0.0), (1e-4, 1e-4, 0.0), (1e-3, 1e-3, 0.0), (0.0, 1.0, 1e-6),
                                               (0.0, 1.0, 1e-3), (1e-8, 1e-8, 1e-2),
-                                              # hundreds of shifts within their own size
                                               (1e-6, 1e-9, 0.0), (1e-4, 1e-7, 0.0)])
 def test_out_of_order(driver, S, jump, period, lost):
     """The ray at a bracket's lower end ends inside and the one at its upper end
     escapes; a direction seen to be out of order ends with multisection's bracket,
-    whatever guided passes before had settled."""
+    whatever guided passes before had settled, or multisection's is decided by an edge
+    beyond the range in which those that they left out were traced."""
     a = rows(S, 1500, 1e-10, jump, period, lost)
     d = driver(a)
     seen = d[:, 4] != 0
     assert seen.sum() > 20
     assert not any(escapes(x, y) for x, y in zip(a, d[:, 0])) and all(escapes(x, y) for x, y in zip(a, d[:, 1]))
-    assert [tuple(x) for x in d[seen, :2]] == [multisection(x) for x in a[seen]]
+    ref = np.array([multisection(x) for x in a[seen]])
+    same = (d[seen, :2] == ref).all(axis=1)
+    assert (same | (ref[:, 1] < d[seen, 5]) | (ref[:, 0] > d[seen, 6])).all()
+    assert same.all() or jump > 100 * period   # (hundreds of shifts within their own size)
 
 
 @pytest.mark.parametrize("S", [16, 64])
@@ -102,4 +105,4 @@ def test_direction_length(driver, S, length):
     scaled[:, 9] = length
     d, e = driver(a), driver(scaled)
     assert np.array_equal(d[:, :2], e[:, :2] * length)
-    assert np.array_equal(d[:, 2:], e[:, 2:])
+    assert np.array_equal(d[:, 2:5], e[:, 2:5])
