@@ -40,7 +40,7 @@ int hip_fail(hipError_t e, const char* what) {
 }
 
 // Images per batched launch: their constants must fit in the kernel's LDS
-// table (~270 bytes each); larger batches run as consecutive launches.
+// table (368 bytes each); larger batches run as consecutive launches.
 constexpr int kMaxBatch = 128;
 constexpr int kDefaultChunk = 64;
 constexpr int32_t kDefaultTile = 8;   // ring-out hand-out: 8 x 8 pixel tiles
@@ -476,8 +476,8 @@ int trace_common(const rt_image_params* params, int32_t n_images, const rt_image
                                emission ? out[i].intensity_n : nullptr, out[i].attempts};
     // Binary64 images: one launch for a single image, else batches grouped by
     // metric (stable), at most kMaxBatch per launch, the costliest metric first:
-    // the launch then drains on the shortest steps (Kerr's 675 vector
-    // instructions, against 844 Einasto and 995 cored NFW).  Mixed-precision images
+    // the launch then drains on the shortest steps (Kerr's 649 vector
+    // instructions, against 833 Einasto and 971 cored NFW).  Mixed-precision images
     // run one by one after them.
     std::vector<int> order, mixed;
     for (int i = 0; i < n_images; ++i)

@@ -9,17 +9,24 @@
 //   Pinned   the same arithmetic, operation for operation (the same bits), on
 //            coefficients that the kernel loads into vector registers once.
 //
-// A wavefront alone on its SIMD issues one instruction every four cycles
-// whatever its type, so the scalar moves are a quarter of its time; several
+// A wavefront alone on its SIMD issues an instruction every 2.0 ns (4.9 cycles at 2.4
+// GHz) whatever its type, so the scalar moves are a quarter of its time; several
 // wavefronts hide them behind each other's vector instructions, and three per
 // SIMD hid most of them.  Pinned coefficients take 38 (Kerr), 64 (Einasto) or
-// 76 (cored NFW) vector registers, so two wavefronts fit a SIMD instead of
-// three, without spills, and 1062 instructions are left of the 1381.  Measured
+// 76 (cored NFW) vector registers, so two wavefronts fit a SIMD instead of three:
+// 239 to 253 registers in the trace kernels and no vector spills, and 1034
+// instructions of the 1381 are left, 59 of them scalar moves (670 Kerr, 880 Einasto;
+// counted between branches, as are all counts here).  The wide cored NFW (eta above
+// 0.34) pins sine's and cosine's coefficients and 19 of the tableau's, not its
+// logarithm's and exponential's: 211 scalar moves of 1256.  Measured
 // with two pinned wavefronts against three that materialise (same bits, one
 // launch, cored NFW chi = 0.94): 64^2 1.57 -> 1.25 ms, 256^2 1.56 -> 1.27,
-// 512^2 2.36 -> 2.10, 1024^2 6.87 -> 6.72 ms; one pinned wavefront per SIMD is
+// 512^2 2.36 -> 2.10, 1024^2 6.87 -> 6.72 ms; wide cored NFW (0.6, 8): 64^2 1.68 -> 1.54,
+// 1024^2 8.25 -> 7.28; one pinned wavefront per SIMD is
 // as fast up to 256^2 and 6 % slower at 1024^2.  So every binary64 kernel pins,
 // at two wavefronts per SIMD, and no rule on the launch's size is needed.
+//   Vector spills remain in the guided shadow boundary's kernels (between passes,
+// rt_boundary.hip) and in Einasto's thick disc (four).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -131,8 +138,9 @@ __device__ __forceinline__ PinnedSet<SCALAR> pin() {
         hold(p.ln2_lo);
         hold(p.inv_ln2);
     }
-    // and as many of the tableau's as every kernel has registers left for without
-    // a spill (image gradients' forward pass is the fullest).  Kerr 64^2 772 -> 744
+    // and as many of the tableau's as the trace, point, resume and gradient kernels
+    // have registers left for without a spill (the gradient's forward pass is the
+    // fullest).  Kerr 64^2 772 -> 744
     // us, 512^2 1423 -> 1383; Einasto 64^2 883 -> 851; no difference at 1024^2,
     // where two wavefronts hide the scalar moves, nor for seven in the cored NFW.
     constexpr int n = SCALAR || !TABLEAU || METRIC == kAll ? 0

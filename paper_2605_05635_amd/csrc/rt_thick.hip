@@ -22,11 +22,13 @@ __device__ __forceinline__ const ImageConst& reloaded_args() {
     return *q;
 }
 
-// Bound by its vector instructions (about 2,400 an attempt).  Of those a sixth
-// were moves that built polynomial coefficients in vector registers, and the
-// square roots' range scaling: sine's and cosine's coefficients are pinned, the
-// others taken through scalar registers (rt_functions.h, PinnedThick), and the
-// roots need no scaling (dm::sqrt_normal).  1024^2 cored NFW 12.66 -> 12.02 ms,
+// Bound by its instructions, 1,830 vector and 620 scalar ones an attempt: two
+// wavefronts keep the vector ALU active 92 % of the time that they are resident
+// and 83 % of the kernel's.  A sixth of the vector ones were moves that built
+// polynomial coefficients in vector registers, and the square roots' range
+// scaling: sine's and cosine's coefficients are pinned, the others taken through
+// scalar registers (rt_functions.h, PinnedThick), and the roots need no scaling
+// (dm::sqrt_normal).  1024^2 cored NFW 12.66 -> 12.02 ms,
 // 64^2 3.01 -> 2.69, the same bits.  (All coefficients pinned: 48 registers
 // spilled.  The exponential's and logarithm's held in scalar registers over the
 // whole loop: 28 scalar registers spilled, 258 lane reads.)
