@@ -670,14 +670,6 @@ def shadow_measurement(steps: int, cpu: bool) -> dict:
     b.record(stream)
     torch.cuda.synchronize()
     ms = a.elapsed_time(b) / steps
-    # without the counts the same brackets come from guided passes
-    rt.rt_shadow_boundary(p, d, b_lo, b_hi, b_tol, out, st, None, stream, samples=S)
-    a.record(stream)
-    for _ in range(steps):
-        rt.rt_shadow_boundary(p, d, b_lo, b_hi, b_tol, out, st, None, stream, samples=S)
-    b.record(stream)
-    torch.cuda.synchronize()
-    guided_ms = a.elapsed_time(b) / steps
     bc = out.mean(dim=1).cpu().numpy()
     passes = int(np.ceil(np.log((b_hi - b_lo) / b_tol) / np.log(S + 1.0)))
     rays = n * S * passes + 2 * n
@@ -691,7 +683,6 @@ def shadow_measurement(steps: int, cpu: bool) -> dict:
     res = {"workload": "cored-NFW benchmark spacetime, 4096 directions, b in [2, 9], "
                        f"bracket 1e-10 ({S}-point multisection)", "samples": S,
            "ms": ms, "directions_per_s": n / ms * 1e3, "steps": steps,
-           "guided_ms": guided_ms, "guided_directions_per_s": n / guided_ms * 1e3,
            "passes": passes, "rays_traced": rays, "attempts_per_ray": attempts / rays,
            "algorithmic_tflops": tflops, "frac_of_fp64_vector_peak": tflops / FP64_VECTOR_PEAK_TFLOPS,
            "all_found": bool((st == 0).all().item()),

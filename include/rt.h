@@ -299,28 +299,12 @@ int rt_refine_points(const rt_image_params *params, const uint8_t *ncross, const
  * X = b cos psi, Y = b sin psi turn from captured to escaping (a ray escapes
  * when it reaches r_esc_fac R_o; captured rays and rays ending otherwise count
  * as inside).  Multisection: the bracket [lo, hi] starts at [b_lo, b_hi];
- * each level divides it at b_j = lo + j w, w = (hi - lo)/(S + 1), j = 1..S with
- * S = samples (64, 32 or 16), and keeps [b_{j-1}, b_j] around the first
- * escaping b_j (b_0 = lo), or [b_S, hi] if none escapes, while hi - lo > b_tol (at most 64 levels, and
- * none once one leaves the bracket unchanged).  Rays are traced as by
+ * each pass traces S = samples (64, 32 or 16) rays at b_j = lo + j w,
+ * w = (hi - lo)/(S + 1), j = 1..S, and keeps [b_{j-1}, b_j] around the first
+ * escaping sample (b_0 = lo), or [b_S, hi] if none escapes, while hi - lo > b_tol (at most 64 passes, and
+ * none once a pass leaves the bracket unchanged).  Rays are traced as by
  * rt_trace_image in binary64 (params->precision must be RT_FP64; the screen
  * fields are validated but not used).
- *   With attempts given, or max(rtol, atol) > 1e-7, every pass traces the S
- * rays of one level, and the bracket is the one above.  With attempts NULL and
- * max(rtol, atol) <= 1e-7 a pass may trace the edges of two or three levels that
- * lie around a prediction of the transition, and leave the others out.  Then
- *   - the bracket is always a cell of that division, the ray at lo ends inside and
- *     the ray at hi escapes;
- *   - it is the bracket above wherever fates are in order along the direction,
- *     inside below the transition and escaping above it;
- *   - a direction in which a traced ray is out of order, or runs out of attempts
- *     or ends by a non-finite estimate, goes on by passes of single levels, from the
- *     last bracket that such passes reached; after rays out of order from the
- *     bracket at hand if the edges left out, as far as 16 times the extent of what
- *     is out of order, are traced and end as it supposes;
- *   - where rays out of order were all left out, the bracket can be at another
- *     transition within the integration's error of the first (none of 690,000
- *     directions at tolerances of 1e-8 and 1e-7 was).
  *   dirs    device [n][2] (cos psi, sin psi); any length, the ray starts from
  *           b times it
  *   out     device [n][2] the final bracket (lo, hi); the boundary point of
@@ -328,7 +312,6 @@ int rt_refine_points(const rt_image_params *params, const uint8_t *ncross, const
  *   status  device [n]: 0, or 1 where the ray at b_lo escapes or the one at
  *           b_hi does not (out is then b_lo, b_hi)
  *   attempts device [n] step attempts of all the direction's rays, or NULL
- *           (see above: counting selects passes of single levels)
  * Asynchronous on the stream; no scratch.  RT_ERR_ARG for null pointers,
  * n outside [1, 2^24], samples not 16, 32 or 64, b_lo <= 0, b_lo >= b_hi, b_tol < 1e-13 b_hi or
  * non-finite values. */
@@ -342,8 +325,8 @@ int rt_shadow_boundary(const rt_image_params *params, const double *dirs, int32_
  * long as its slowest ray, the one that winds longest near the photon shell:
  * while the device has idle SIMDs, more samples (fewer passes) finish first;
  * once it is full, fewer samples waste less of each pass (256 compute units,
- * cored NFW, guided passes, ms at S = 64 / 32 / 16: 11.0 / 12.1 / 13.0 for 1024
- * directions, 27.2 / 38.2 / 14.9 for 4096, 81 / 63 / 40 for 16384).  Returns 16, 32 or
+ * cored NFW, ms at S = 64 / 32 / 16: 14.2 / 19.4 / 20.2 for 1024 directions, 37.0 /
+ * 36.0 / 21.8 for 4096, 120 / 89 / 55 for 16384).  Returns 16, 32 or
  * 64; RT_ERR_ARG for n < 1, RT_ERR_HIP if the device cannot be queried. */
 int rt_shadow_boundary_samples(int32_t n);
 

@@ -25,8 +25,7 @@
 // 1024^2 8.25 -> 7.28; one pinned wavefront per SIMD is
 // as fast up to 256^2 and 6 % slower at 1024^2.  So every binary64 kernel pins,
 // at two wavefronts per SIMD, and no rule on the launch's size is needed.
-//   Vector spills remain in the guided shadow boundary's kernels (between passes,
-// rt_boundary.hip) and in Einasto's thick disc (four).
+//   Vector spills remain in Einasto's thick disc (four).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -109,7 +108,7 @@ using PinnedThick = PinnedSet<true>;
 // The coefficients as the kernel of a metric holds them: in vector registers,
 // opaque to the compiler so that it cannot turn them back into literals.
 constexpr int kAll = -1;   // every metric's coefficients (the batched kernel)
-template <int METRIC, bool SCALAR = false, bool TABLEAU = true>
+template <int METRIC, bool SCALAR = false>
 __device__ __forceinline__ PinnedSet<SCALAR> pin() {
     PinnedSet<SCALAR> p;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -138,16 +137,15 @@ __device__ __forceinline__ PinnedSet<SCALAR> pin() {
         hold(p.ln2_lo);
         hold(p.inv_ln2);
     }
-    // and as many of the tableau's as the trace, point, resume and gradient kernels
-    // have registers left for without a spill (the gradient's forward pass is the
-    // fullest).  Kerr 64^2 772 -> 744
+    // and as many of the tableau's as every kernel has registers left for without
+    // a spill (the gradient's forward pass is the fullest).  Kerr 64^2 772 -> 744
     // us, 512^2 1423 -> 1383; Einasto 64^2 883 -> 851; no difference at 1024^2,
     // where two wavefronts hide the scalar moves, nor for seven in the cored NFW.
-    constexpr int n = SCALAR || !TABLEAU || METRIC == kAll ? 0
-                      : METRIC == KERR                     ? 23
-                      : METRIC == EINASTO                  ? 10
-                      : METRIC == CNFW_NEAR                ? 0
-                                                           : 19;
+    constexpr int n = SCALAR || METRIC == kAll ? 0
+                      : METRIC == KERR         ? 23
+                      : METRIC == EINASTO      ? 10
+                      : METRIC == CNFW_NEAR    ? 0
+                                               : 19;
     double* const rk[] = {&p.rk.a61, &p.rk.a62, &p.rk.a63, &p.rk.a64, &p.rk.a65, &p.rk.a51, &p.rk.a52,
                           &p.rk.a53, &p.rk.a54, &p.rk.a41, &p.rk.a42, &p.rk.a43, &p.rk.a31, &p.rk.a32,
                           &p.rk.b1,  &p.rk.b3,  &p.rk.b4,  &p.rk.b5,  &p.rk.b6,  &p.rk.e1,  &p.rk.e3,

@@ -90,7 +90,7 @@ template <class K, class S>
 __host__ __device__ __forceinline__ void rhs_at(const K& k, const S& E, const S& L, const S& chiE,
                                                 const S& chiL, const S& R, const S& pR,
                                                 const S& pth, const S& s, const S& co, const S& F,
-                                                const S& dF, S d[6], S* inv_sigma = nullptr) {
+                                                const S& dF, S d[6]) {
     const S half(0.5), two(2.0);
     const S R2 = R * R;
     const S R2c = R2 + k.chi2;
@@ -122,7 +122,6 @@ __host__ __device__ __forceinline__ void rhs_at(const K& k, const S& E, const S&
     const S NiS = N * iS;
     d[4] = (R * NiS - hdN) * iS;
     d[5] = co * iS * (W * (Lis2 + chiE) - k.chi2 * s * NiS);
-    if (inv_sigma) *inv_sigma = iS;
 }
 
 // The same at (R, theta), with sine, cosine and mass function from T
@@ -211,7 +210,6 @@ struct Ray {
     double y[6];    // T, R, theta, phi, p_R, p_theta
     double k1[6];   // f(y), first-same-as-last
     double I, kI;   // thick disc: intensity so far and g^3 j at y (THICK attempts only)
-    double tau, iS; // int dlambda / Sigma so far and 1/Sigma at y (CLOCK attempts only)
     double E, L, chiE, chiL;
     double h, lam, last_cross;
     double rc[3];   // radii of the first three trusted crossings
@@ -346,8 +344,7 @@ __host__ __device__ __forceinline__ void start_ray_dir(const ImageConst& c, cons
     r.y[3] = 0.0;
     r.y[4] = c.obs_sq_gRR * n.nR;
     r.y[5] = c.obs_sq_gthth * n.nth;
-    rhs_at(k, r.E, r.L, r.chiE, r.chiL, r.y[1], r.y[4], r.y[5], a.s, a.co, a.F, a.dF, r.k1, &r.iS);
-    r.tau = 0.0;
+    rhs_at(k, r.E, r.L, r.chiE, r.chiL, r.y[1], r.y[4], r.y[5], a.s, a.co, a.F, a.dF, r.k1);
     r.h = c.h0;
     r.lam = 0.0;
     r.last_cross = -INFINITY;
@@ -556,10 +553,8 @@ struct StageNone {
 
 // THICK: the thick disc's intensity as a seventh component (dI/dlambda =
 // thick_source, no feedback), in the error norm with the other six.
-// CLOCK: no crossings (only the ray's fate is wanted), and r.tau accumulates int
-// dlambda / Sigma with the step's own weights, the parameter in which the radial
-// motion does not see the polar one.
-template <int METRIC, class Sink = StageNone, bool THICK = false, class T = fn::Direct, bool CLOCK = false>
+// FATE: no crossings (only how the ray ends is wanted).
+template <int METRIC, class Sink = StageNone, bool THICK = false, class T = fn::Direct, bool FATE = false>
 __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs& o, int64_t n_pix,
                                                     Ray& r, Sink sink = Sink{}, const T& tb = T{}) {
     if (r.attempts >= k.max_attempts) return RAY_STEP_LIMIT;
@@ -575,7 +570,6 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
         ae[i] = e1 * r.k1[i];
         ad[i] = d1 * r.k1[i];
     }
-    double abS = CLOCK ? b1 * r.iS : 0.0, iS_ = 0.0;   // CLOCK: sum of b_i / Sigma_i, 1/Sigma at the last stage
     double abI = 0.0, aeI = 0.0;   // THICK: sums of b_i kI_i, e_i kI_i
     if constexpr (THICK) {
         abI = b1 * r.kI;
@@ -589,10 +583,6 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
         fn::signed_sincos(tb, x[2], &s_, &co_);                                  \
         fn::mass_function<METRIC>(tb, k, x[1], F_, dF_);                         \
         rhs_at(k, r.E, r.L, r.chiE, r.chiL, x[1], x[4], x[5], s_, co_, F_, dF_, out); \
-    } else if constexpr (CLOCK) {                                                \
-        fn::sincos(tb, x[2], &s_, &co_);                                         \
-        fn::mass_function<METRIC>(tb, k, x[1], F_, dF_);                         \
-        rhs_at(k, r.E, r.L, r.chiE, r.chiL, x[1], x[4], x[5], s_, co_, F_, dF_, out, &iS_); \
     } else {                                                                     \
         rhs_c<METRIC>(k, r.E, r.L, r.chiE, r.chiL, x[1], x[2], x[4], x[5], out, tb); \
     }
@@ -608,7 +598,6 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     for (int i = 0; i < 6; ++i) t[i] = r.y[i] + h * (expr);                       \
     RT_RHS(t, out)
 #define RT_ACC(bb, ee, dd, kv)                                                   \
-    if constexpr (CLOCK) abS += bb * iS_;                                        \
     for (int i = 0; i < 6; ++i) {                                                \
         ab[i] += bb * kv[i];                                                     \
         ae[i] += ee * kv[i];                                                     \
@@ -675,8 +664,8 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     r.after_reject = 0;
 
     // Equatorial crossing (Sec. 3.3): theta's band index changes.
-    const double band0 = CLOCK ? 0.0 : equator_band(r.y[2]);
-    const double band1 = CLOCK ? 0.0 : equator_band(yn[2]);
+    const double band0 = FATE ? 0.0 : equator_band(r.y[2]);
+    const double band1 = FATE ? 0.0 : equator_band(yn[2]);
     if (band0 != band1) {
         const Passage ps = passage_of(band0, band1);
         auto dense = [&](int i) {
@@ -718,10 +707,6 @@ __host__ __device__ __forceinline__ int32_t attempt(const Hot& k, const OutPtrs&
     if constexpr (THICK) {
         r.I = ynI;
         r.kI = kI7;
-    }
-    if constexpr (CLOCK) {
-        r.tau += h * abS;
-        r.iS = iS_;
     }
     r.lam += h;
     r.h = h * factor;
