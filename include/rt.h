@@ -325,8 +325,8 @@ int rt_shadow_boundary(const rt_image_params *params, const double *dirs, int32_
  * long as its slowest ray, the one that winds longest near the photon shell:
  * while the device has idle SIMDs, more samples (fewer passes) finish first;
  * once it is full, fewer samples waste less of each pass (256 compute units,
- * cored NFW, ms at S = 64 / 32 / 16: 14.2 / 19.4 / 20.2 for 1024 directions, 37.0 /
- * 36.0 / 21.8 for 4096, 120 / 89 / 55 for 16384).  Returns 16, 32 or
+ * cored NFW, ms at S = 64 / 32 / 16: 14.5 / 19.7 / 20.1 for 1024 directions, 37.9 /
+ * 36.6 / 22.0 for 4096, 121 / 90 / 57 for 16384).  Returns 16, 32 or
  * 64; RT_ERR_ARG for n < 1, RT_ERR_HIP if the device cannot be queried. */
 int rt_shadow_boundary_samples(int32_t n);
 

@@ -12,8 +12,8 @@
 //
 // Bound by the longest direction's chain: 4096 directions at S = 16 are one
 // wavefront per SIMD, and next to the polar axis nine passes take up to 9623
-// attempts one after another, 2.2 us each: 23.1 -> 21.7 ms with pinned coefficients
-// and without the crossings, 1000 at S = 64 15.0 -> 14.1 (cored NFW chi = 0.94).
+// attempts one after another, 2.2 us each: 23.4 -> 22.0 ms with pinned coefficients
+// and without the crossings, 500 at S = 64 14.9 -> 14.2 (cored NFW chi = 0.94).
 // Every pass traces all edges of one level.  Passes that sampled edges two or three
 // levels down around a predicted transition took 15 ms, but fates are not in order
 // next to the axis, within 1e-5 M of the transition: 658 of 73,728 directions
